@@ -13,6 +13,7 @@ running row maximum over 64-key tiles, Algorithm 1's (or exp-then-quantize's)
 codes and E8M0 scales per 32 keys, and the products with the MXFP4 value
 operand (and MXFP8 Q and K on the low-bit path).
 """
+import ctypes
 import math
 
 import numpy as np
@@ -124,7 +125,8 @@ def prepare(case, seed):
     if c["op"] in ("attn", "vhat", "lowbit"):
         s["out"] = torch.empty(q.shape, dtype=torch.float32, device="cuda")
     if c["op"] == "attn":
-        s["ws"] = torch.empty(binding.vhat_bytes(sh), dtype=torch.uint8, device="cuda")
+        n = binding.lib().efq_attn_workspace_bytes(ctypes.byref(sh))
+        s["ws"] = torch.empty(n, dtype=torch.uint8, device="cuda")
     elif c["op"] == "lowbit":
         s["ws"] = torch.empty(binding.lowbit_workspace_bytes(sh), dtype=torch.uint8, device="cuda")
     elif c["op"] == "vhat":
