@@ -57,6 +57,7 @@ constexpr float kLn6 = 1.79175946922805500081f;      // log 6, Eq. (z-def)
 
 constexpr int kWaveQ = 32;     // queries per wave (MFMA N)
 constexpr int kBc = 64;        // keys per tile (two 32-key microscaling blocks)
+constexpr int kXcdCUs = 32;    // compute units of one of the 8 XCDs
 
 // C16 fold table of EFQ-Softmax-LUT (Sec. II-D) as bytes: byte j of the
 // 16-byte table (little-endian dwords kC16T0..3) is C16[j].
@@ -138,7 +139,8 @@ __host__ __device__ constexpr int key_nibble(int t) {
 // The stage is split into pieces so the fused kernel can interleave them
 // with the matrix-core work of the next tile:
 //   pg_max     partial block maxima of the lane's 32 scores
-//   pg_params  row maximum, its change, and the per-block parameters (Alg. 1:
+//   pg_rowmax  the tile's row maximum
+//   pg_params  the change of the row maximum, and the per-block parameters (Alg. 1:
 //              M_b, k_b, and the affine bias; or the exp-then-quantize scale)
 //   pg_alpha   alpha from the change (the fused kernel forms it only when
 //              some row maximum of the wave moved)
@@ -187,9 +189,29 @@ __device__ __forceinline__ void pg_max(const f32x16& s0, const f32x16& s1, float
 template <int KIND>
 constexpr bool is_expq() { return KIND == EFQ_PGEN_EXPQ || KIND == EFQ_PGEN_EXPQ6; }
 
-// Returns whether some row maximum of the wave moved (wave-uniform).
+// The maximum of a query's 64 scores (rowmax S^j, in the stage's units) and
+// bs, that of the lane's own block.
 template <int KIND>
-__device__ __forceinline__ bool pg_params(float pm0, float pm1, float& m, const PgenArgs& pa,
+__device__ __forceinline__ float pg_rowmax(float pm0, float pm1, const PgenArgs& pa, float& bs) {
+  if constexpr (KIND == EFQ_PGEN_NOOP) {
+    return bs = 0.0f;
+  } else {
+    const float unit = is_expq<KIND>() ? pa.l2s : pa.scale;
+    swap32f(pm0, pm1);                          // lower: (own, partner) block 0; upper: block 1
+    const float bmine = fmax_swapped(pm0, pm1);  // raw maximum of the lane's own block
+    // the lane's block maximum in score units; rounding is monotone, so the
+    // row maximum of the products is the product of the raw row maximum
+    bs = bmine * unit;
+    float t0 = bs, t1 = bs;
+    swap32f(t0, t1);                            // (block 0 max, block 1 max) in every lane
+    return fmax_swapped(t0, t1);                // rowmax S^j
+  }
+}
+
+// The block parameters, with the new running maximum mnew.  Returns whether
+// some row maximum of the wave moved (wave-uniform).
+template <int KIND>
+__device__ __forceinline__ bool pg_params(float bs, float mnew, float& m, const PgenArgs& pa,
                                           PgenState& st) {
   bool moved = false;
   if constexpr (KIND == EFQ_PGEN_NOOP) {
@@ -198,18 +220,6 @@ __device__ __forceinline__ bool pg_params(float pm0, float pm1, float& m, const 
     st.w[0] = st.w[1] = st.w[2] = st.w[3] = 0x22222222u;
     return moved;
   } else {
-    constexpr bool LOG2 = is_expq<KIND>();
-    const float unit = LOG2 ? pa.l2s : pa.scale;
-    swap32f(pm0, pm1);                          // lower: (own, partner) block 0; upper: block 1
-    const float bmine = fmax_swapped(pm0, pm1);  // raw maximum of the lane's own block
-    // the lane's block maximum in score units; rounding is monotone, so the
-    // row maximum of the products is the product of the raw row maximum
-    const float bs = bmine * unit;
-    float t0 = bs, t1 = bs;
-    swap32f(t0, t1);                            // (block 0 max, block 1 max) in every lane
-    const float mt = fmax_swapped(t0, t1);      // rowmax S^j
-    // m is itself a maximum (or -inf), so no operand quieting is needed
-    const float mnew = fmax_swapped(m, mt);
     // alpha (pg_alpha) is formed only where a row maximum moved
     st.dm = m - mnew;
     moved = __builtin_amdgcn_ballot_w64(m != mnew) != 0ull;
@@ -378,7 +388,10 @@ __device__ __forceinline__ PgenOut pgen(const f32x16& s0, const f32x16& s1, floa
   float pm0, pm1;
   PgenState st;
   pg_max<KIND>(s0, s1, pm0, pm1);
-  pg_params<KIND>(pm0, pm1, m, pa, st);
+  float bs;
+  const float mt = pg_rowmax<KIND>(pm0, pm1, pa, bs);
+  // m is itself a maximum (or -inf), so no operand quieting is needed
+  pg_params<KIND>(bs, fmax_swapped(m, mt), m, pa, st);
   pg_pairs<KIND, 0, 32>(s0, s1, pa, st);
   if constexpr (KIND == EFQ_PGEN_NOOP) asm volatile("" ::"v"(s0), "v"(s1));   // keep Q K^T live
   return pg_finish<KIND>(st);
@@ -558,6 +571,7 @@ struct AttnArgs {
   size_t scale_off;   // byte offset of the E8M0 plane in V~
   int nqt;            // query tiles per (batch, head)
   int xcd_remap;      // 1: group work items by XCD
+  int spread;         // 1: pair long and short work items (map_work)
   float scale, tau, h;
   // dump (may be null)
   uint8_t* p_codes;
@@ -604,7 +618,7 @@ constexpr int kStampBlocks = 256;
 constexpr int kStampSlots = 2 * kStampPhases + 4;   // per wave: 2 per phase, then the clock pairs
 constexpr int kStampBytes = EFQ_PHASE_STAMPS ? 2 * kStampSlots * 8 : 0;
 
-template <int D, int KS, int VS, bool Q8 = false>
+template <int D, int KS, int VS, bool Q8 = false, bool STAMPS = true>
 struct Smem {
   static constexpr int kK = Q8 ? kBc * D + 256 : kBc * D * 2;   // one K tile
   static constexpr int kVc = 2 * D * 16;                 // V~ codes of two blocks
@@ -613,7 +627,7 @@ struct Smem {
   static constexpr int kKOff = 0;
   static constexpr int kVOff = KS * kK;
   static constexpr int kStampOff = KS * kK + VS * kV;
-  static constexpr int kTotal = KS * kK + VS * kV + kStampBytes;
+  static constexpr int kTotal = KS * kK + VS * kV + (STAMPS ? kStampBytes : 0);
 };
 
 // Direct-to-LDS loads (buffer_load ... lds: LDS address = M0 base + size *
@@ -673,7 +687,7 @@ template <int D, int NW>
 struct VLoad {
   static constexpr int kVc = Smem<D, 1, 1>::kVc;         // V~ code bytes per tile
   static constexpr int NB = kVc / 1024;                  // 1 KB code blocks (2 or 4)
-  static_assert(NB < NW, "a wave left over for the scales");
+  static_assert(NB <= NW, "at most one code block per wave");
   const uint8_t* codes;
   const uint8_t* scales;
   int nb;
@@ -714,7 +728,10 @@ template <int D, int NW>
 struct KLoad8 {
   static constexpr int NC = D / 64;                      // 64-column chunks
   static constexpr int NBLK = 4 * NC;                    // 1 KB code blocks per tile
-  static_assert(NBLK <= NW, "one code block per wave");
+  // code blocks per wave: wave, wave + NW, ... (NW blocks on is one 32-key
+  // window on where a wave has two)
+  static constexpr int PER = NBLK > NW ? NBLK / NW : 1;
+  static_assert(PER == 1 || (PER == 2 && NW == 2 * NC), "a wave's second block is its window's twin");
   const void* codes;
   const void* scales;
   unsigned cbytes, sbytes;
@@ -728,10 +745,12 @@ struct KLoad8 {
     const int h = blk & 1, c = (blk >> 1) % NC, w = blk / (2 * NC);
     voff = (32 * w + (lane & 31)) * D + 64 * c + 32 * h + 16 * (lane >> 5);
   }
-  // code block `wave` (waves below NBLK)
+  // code blocks `wave`, `wave` + NW, ... (waves below NBLK)
   __device__ void issue_codes(uint8_t* kbuf, int tile, int wave) const {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(codes, cbytes), kbuf + wave * 1024, 16,
-                                             voff, tile * kBc * D, 0, 0);
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(make_rsrc(codes, cbytes), kbuf + (wave + i * NW) * 1024,
+                                               16, voff + i * 32 * D, tile * kBc * D, 0, 0);
   }
   // 64 keys x D/32 bytes as dwords; for D = 64 the upper lanes read the
   // next tile's scales into the unused half.  The resource starts at the
@@ -786,12 +805,26 @@ __device__ __forceinline__ void wait_vmem_le(int n) {
 // of work items.  Consecutive work items are the query heads of one GQA group
 // at one query tile, then the next tile, so the workgroups that stream the
 // same key/value tiles run side by side on one XCD and share its L2.  Query
-// tiles run longest first.
+// tiles run longest first.  With `spread` (a causal grid of half workgroups
+// that is resident at once, two on a CU) an XCD's items are ordered by length
+// over all its heads and the second 32 (one per CU) reversed, so that a
+// long workgroup shares its CU with a short one: 2 prompts of 1024 tokens
+// 28.2 -> 24.9 us, one of 2048 40.0 -> 38.4 us.
 __device__ __forceinline__ void map_work(const AttnArgs& a, int& b, int& hq, int& qt) {
   const int n = blockIdx.x;
   const int total = gridDim.x;
   int w = n;
   if (a.xcd_remap) w = (n & 7) * (total >> 3) + (n >> 3);
+  if (a.spread) {
+    const int items = total >> 3, heads = items / a.nqt;   // of one XCD
+    int i = n >> 3;
+    if (i >= kXcdCUs) i = kXcdCUs + items - 1 - i;
+    const int bh = (n & 7) * heads + i % heads;
+    qt = a.nqt - 1 - i / heads;
+    hq = bh % a.Hq;
+    b = bh / a.Hq;
+    return;
+  }
   const int G = a.Hq / a.Hkv;
   const int per = G * a.nqt;          // work items of one (batch, kv head)
   const int bg = w / per, r = w % per;
@@ -1161,7 +1194,7 @@ __device__ __forceinline__ PgenOut mma_phase8(const uint8_t* kbuf, const QOps<D,
   return po;
 }
 
-template <int D, int KIND, bool DUMP, bool Q8 = false>
+template <int D, int KIND, bool DUMP, bool Q8, bool PREREAD>
 struct PPWave {
   static constexpr int NS = D / 32;
   QOps<D, Q8> qo;
@@ -1177,7 +1210,7 @@ struct PPWave {
   unsigned klane;         // LDS address of the lane's K operand read in K slot 0
   unsigned vlane, vslane; // of its V~ code and scale reads in V~ slot 0
   // the pre-read needs registers the bf16 exp-then-quantize variants lack
-  static constexpr bool kPreOn = kKPre && (Q8 || EFQ_KPRE_BF16);
+  static constexpr bool kPreOn = PREREAD && kKPre && (Q8 || EFQ_KPRE_BF16);
   static constexpr int kMPrio = KIND == EFQ_PGEN_EFQ ? EFQ_PRIO_EFQ_M
                                 : KIND == EFQ_PGEN_LUT ? EFQ_PRIO_LUT_M
                                 : KIND == EFQ_PGEN_NOOP ? 0 : EFQ_PRIO_OTHER_M;
@@ -1248,9 +1281,11 @@ struct PPWave {
     // some lane's visible keys end inside this tile
     if (j >= mask_from)
       mask_tile(s0, s1, vis_end4 - j * kBc);
-    float pm0, pm1;
+    float pm0, pm1, bs;
     pg_max<KIND>(s0, s1, pm0, pm1);
-    if (pg_params<KIND>(pm0, pm1, m, pa, st)) {
+    const float mt = pg_rowmax<KIND>(pm0, pm1, pa, bs);
+    // m is itself a maximum (or -inf), so no operand quieting is needed
+    if (pg_params<KIND>(bs, fmax_swapped(m, mt), m, pa, st)) {
       const float alpha = pg_alpha<KIND>(st);
 #pragma unroll
       for (int s = 0; s < NS; ++s) oacc[s] *= alpha;
@@ -1296,7 +1331,7 @@ __device__ unsigned long long* g_stamps;   // [kStampBlocks][2 groups][kStampSlo
 #endif
 
 template <int G, int D, int KIND, bool DUMP, bool Q8, typename Stream>
-__device__ __forceinline__ void pp_schedule(PPWave<D, KIND, DUMP, Q8>& w, int T, int ntiles,
+__device__ __forceinline__ void pp_schedule(PPWave<D, KIND, DUMP, Q8, true>& w, int T, int ntiles,
                                             const uint8_t* kbuf0, const uint8_t* vbuf0,
                                             const AttnArgs& a, int b, int hq, int keep,
                                             Stream& stream) {
@@ -1404,28 +1439,103 @@ __device__ __forceinline__ void pp_schedule(PPWave<D, KIND, DUMP, Q8>& w, int T,
   }
 }
 
+// ------------------------------------------------------- half workgroup
+// Four waves (128 queries, one wave per SIMD) and LDS rings small enough for
+// two workgroups on a CU, so the second wave of every SIMD belongs to another
+// workgroup, in another part of its work.  Bound by the latency of a tile's
+// chain (M then V, ~2100 cycles for a wave alone on its SIMD, ~2450 for two)
+// and, with few keys, by the loads and stores around it, which the other
+// workgroup's tiles cover.  Against the eight-wave kernel the K and V~ tiles
+// are read twice as often and a tile costs 5-10 % more in the steady state;
+// it wins where that kernel leaves CUs idle or its workgroups are short
+// (use_half).  Kernel time, EFQ, 32/8 heads, D 128 causal, eight waves ->
+// this: 512 tokens 18.8 -> 13.5 us, 2048 tokens 46.3 -> 41.0 us, 16 prompts
+// of 333 tokens 55.6 -> 41.0 us; 8192 tokens 352 -> 372 us.
+constexpr int kHWaves = 4;
+constexpr int kHP = 2;                     // tiles streamed ahead
+constexpr int kHK = kHP + 1;               // K ring depth
+constexpr int kHV = kHP + 2;               // V~ ring depth
+template <int D, bool Q8 = false>
+using SmemH = Smem<D, kHK, kHV, Q8, false>;
+static_assert(2 * SmemH<128>::kTotal <= 160 * 1024 && 2 * SmemH<128, true>::kTotal <= 160 * 1024,
+              "two half workgroups exceed the LDS of a CU");
+
+// The schedule of a wave of a half workgroup.  Iteration j runs M(j) (with
+// the codes and P~V of tile j-1) and V(j), streams tile j+P, waits until tile
+// j+1 has landed (the loads of the P-1 tiles after it may stay in flight)
+// and ends with a workgroup barrier.  Tile x is read only in iteration x (K
+// by M(x), V~ by V(x)), after the barrier that follows every wave's landing
+// wait for it.  The slots tile j+P overwrites held K(j-1) in a ring of P+1,
+// read and consumed in iteration j-1, and V~(j-2) in a ring of P+2, read in
+// iteration j-2 and consumed by M(j-1) (or F) before the barrier of iteration
+// j-1.  Every wave runs ntiles iterations, so all pass the same barriers;
+// past the last tile the last one is streamed again, so the wait is a
+// constant.
+template <int D, int KIND, bool Q8, int LOADS, typename Stream>
+__device__ __forceinline__ void half_schedule(PPWave<D, KIND, false, Q8, false>& w, int T, int ntiles,
+                                              const uint8_t* kbuf0, const uint8_t* vbuf0,
+                                              const AttnArgs& a, Stream& stream) {
+  using Sm = SmemH<D, Q8>;
+  f32x16 sa0, sa1, sb0, sb1;
+  VOps<D> vop;
+  KPre<D, Q8> kp;
+  int kr = 0, vr = 0;
+  const int mask_from = __builtin_amdgcn_readfirstlane(w.vis_min) / kBc;
+  auto end = [&]() {
+    __builtin_amdgcn_sched_barrier(0);
+    stream();
+    kr = ring_next<Sm::kK, kHK>(kr);
+    vr = ring_next<Sm::kV, kHV>(vr);
+    wait_vmem_le((kHP - 1) * LOADS);
+    wg_barrier();
+  };
+  w.template mphase<true, false, false>(0, kbuf0, kr, vop, kp, a, 0, 0, sa0, sa1, sb0, sb1);
+  w.vphase(0, vbuf0, vr, kbuf0, kr, sa0, sa1, vop, kp, mask_from);
+  end();
+  int j = 1;
+  for (; j + 1 < T; j += 2) {
+    w.template mphase<true, true, false>(j, kbuf0, kr, vop, kp, a, 0, 0, sb0, sb1, sa0, sa1);
+    w.vphase(j, vbuf0, vr, kbuf0, kr, sb0, sb1, vop, kp, mask_from);
+    end();
+    w.template mphase<true, true, false>(j + 1, kbuf0, kr, vop, kp, a, 0, 0, sa0, sa1, sb0, sb1);
+    w.vphase(j + 1, vbuf0, vr, kbuf0, kr, sa0, sa1, vop, kp, mask_from);
+    end();
+  }
+  if (j < T) {   // one more tile: its scores go to set b, the last coded from b
+    w.template mphase<true, true, false>(j, kbuf0, kr, vop, kp, a, 0, 0, sb0, sb1, sa0, sa1);
+    w.vphase(j, vbuf0, vr, kbuf0, kr, sb0, sb1, vop, kp, mask_from);
+    end();
+    w.template mphase<false, true, false>(T, kbuf0, kr, vop, kp, a, 0, 0, sa0, sa1, sb0, sb1);
+  } else {       // the last tile's scores are in set a
+    w.template mphase<false, true, false>(T, kbuf0, kr, vop, kp, a, 0, 0, sb0, sb1, sa0, sa1);
+  }
+  for (int t = T; t < ntiles; ++t) end();
+}
+
+// The body of the attention kernels: NW = 8 waves in the ping-pong schedule,
+// or NW = 4 in the half workgroup's.
 // Q8: q and k are the MXFP8 buffers Q^ and K^ (E4M3 codes, then E8M0 scales
 // at a.q8_soff / a.k8_soff, [batch][head][padded seq] rows), else bf16 BSHD.
-template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8>
-__global__ __attribute__((amdgpu_flat_work_group_size(kPPThreads, kPPThreads),
-                          amdgpu_waves_per_eu(2, 2))) void
-attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
-               const uint8_t* __restrict__ vhat, float* __restrict__ out, AttnArgs a) {
-  extern __shared__ __align__(16) uint8_t smem[];
+template <int NW, int D, int KIND, bool CAUSAL, bool DUMP, bool Q8>
+__device__ __forceinline__ void attn_body(const void* __restrict__ q, const void* __restrict__ k,
+                                          const uint8_t* __restrict__ vhat,
+                                          float* __restrict__ out, const AttnArgs& a,
+                                          uint8_t* smem) {
+  constexpr bool kPair = NW == kPPWaves;     // the ping-pong schedule
+  constexpr int kBr = kWaveQ * NW;           // queries per workgroup
   constexpr int KK = D / 16;
   constexpr int NS = D / 32;
-  using Sm = SmemPP<D, Q8>;
+  using Sm = std::conditional_t<kPair, SmemPP<D, Q8>, SmemH<D, Q8>>;
 
   int b, hq, qt;
   map_work(a, b, hq, qt);
   const int g = hq / (a.Hq / a.Hkv);
   // wave index as a uniform (scalar) value: the group branch below is uniform
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int group = wave >> 2;
-  PPWave<D, KIND, DUMP, Q8> w;
+  PPWave<D, KIND, DUMP, Q8, kPair> w;
   w.lane = threadIdx.x & 63;
   w.half = w.lane >> 5;
-  const int q_wave0 = qt * kPPBr + wave * kWaveQ;
+  const int q_wave0 = qt * kBr + wave * kWaveQ;
   w.my_q = q_wave0 + (w.lane & 31);
   const int q_load = w.my_q < a.Sq ? w.my_q : a.Sq - 1;
   if constexpr (Q8) {
@@ -1451,7 +1561,7 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
     for (int kk = 0; kk < KK; ++kk) w.qo.r[kk] = *(const bf16x8*)(qp + kk * 16);
   }
   // tiles of the workgroup and of this wave (1 <= wtiles <= ntiles)
-  const int kv_end = CAUSAL ? min(a.Sk, qt * kPPBr + kPPBr) : a.Sk;
+  const int kv_end = CAUSAL ? min(a.Sk, qt * kBr + kBr) : a.Sk;
   const int wave_end = CAUSAL ? min(a.Sk, q_wave0 + kWaveQ) : a.Sk;
   const int ntiles = (kv_end + kBc - 1) / kBc;
   const int wtiles = (wave_end + kBc - 1) / kBc;
@@ -1467,7 +1577,7 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
   w.vslane = lds_addr(vbuf0 + vscale_offset<D>(w.lane));
   asm volatile("" : "+v"(w.klane), "+v"(w.vlane), "+v"(w.vslane));
 
-  std::conditional_t<Q8, KLoad8<D, kPPWaves>, KLoad<D, kPPWaves>> kload;
+  std::conditional_t<Q8, KLoad8<D, NW>, KLoad<D, NW>> kload;
   if constexpr (Q8) {
     const uint8_t* kh = (const uint8_t*)k;
     const long hrow = ((long)b * a.Hkv + g) * a.sk_pad;
@@ -1475,7 +1585,7 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
   } else {
     kload.init((const unsigned short*)k + (long)b * a.Sk * a.Hkv * D, a.Sk, a.Hkv, g, wave, w.lane);
   }
-  using VL = VLoad<D, kPPWaves>;
+  using VL = VLoad<D, NW>;
   VL vload;
   vload.init(vhat + ((long)b * a.Hkv + g) * a.nb * D * 16,
              vhat + a.scale_off + ((long)b * a.Hkv + g) * a.nb * D, a.nb, w.lane);
@@ -1498,15 +1608,27 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
   // K^ codes and scales) and V~ codes and scales.  Every wave issues kLoads
   // loads: its K blocks and one V~ code block, or, where a wave has fewer,
   // a copy of a scale load (several waves write the same bytes to the same
-  // place).  Past the last tile (x >= ntiles) the last tile is loaded
-  // again, so the count never changes and the waits are constants.
-  constexpr int kLoads = Q8 ? 2 : KLoad<D, kPPWaves>::kIssued + 1;
+  // place); the four waves of a half workgroup all load the scales too.
+  // Past the last tile (x >= ntiles) the last tile is loaded again, so the
+  // count never changes and the waits are constants.
+  constexpr int kLoads = Q8 ? (kPair ? 2 : KLoad8<D, NW>::PER + 3)
+                            : KLoad<D, NW>::kIssued + (kPair ? 1 : 2);
   auto load_tile = [&](int x, int kofs, int vofs) {
     const int xt = x < ntiles ? x : ntiles - 1;
     uint8_t* const kb = kbuf0 + kofs;
     uint8_t* const vb = vbuf0 + vofs;
-    if constexpr (Q8) {
-      using K8 = KLoad8<D, kPPWaves>;
+    if constexpr (!kPair) {
+      if constexpr (Q8) {
+        kload.issue_codes(kb, xt, wave);
+        kload.issue_scales(kb, xt, w.lane);
+      } else {
+        kload.issue(kb, xt, wave);
+      }
+      if (wave < VL::NB) vload.issue_codes(vb, xt, wave);
+      else vload.issue_scales(vb, xt);
+      vload.issue_scales(vb, xt);
+    } else if constexpr (Q8) {
+      using K8 = KLoad8<D, NW>;
       // waves with a K^ code block: that and a V~ code block or a scale
       // load; the others (D = 64) two scale loads
       if (wave < K8::NBLK) kload.issue_codes(kb, xt, wave);
@@ -1521,6 +1643,23 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
       else vload.issue_scales(vb, xt);
     }
   };
+  if constexpr (!kPair) {
+    // prologue: tiles 0 .. P-1; tile 0 resident, the others in flight
+#pragma unroll
+    for (int x = 0; x < kHP; ++x) load_tile(x, x * Sm::kK, x * Sm::kV);
+    wait_vmem_le((kHP - 1) * kLoads);
+    __syncthreads();
+    int sx = kHP;
+    int skofs = (kHP % kHK) * Sm::kK, svofs = (kHP % kHV) * Sm::kV;
+    auto stream = [&]() {
+      load_tile(sx, skofs, svofs);
+      ++sx;
+      skofs = ring_next<Sm::kK, kHK>(skofs);
+      svofs = ring_next<Sm::kV, kHV>(svofs);
+    };
+    half_schedule<D, KIND, Q8, kLoads>(w, wtiles, ntiles, kbuf0, vbuf0, a, stream);
+  } else {
+  const int group = wave >> 2;
   // prologue: tiles 0 .. P; tiles 0 and 1 resident, 2 .. P in flight (the
   // loads of the last P-1 even phases before phase 2)
 #pragma unroll
@@ -1551,9 +1690,11 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
     pp_schedule<0>(w, wtiles, ntiles, kbuf0, vbuf0, a, b, hq, keep, stream);
   else
     pp_schedule<1>(w, wtiles, ntiles, kbuf0, vbuf0, a, b, hq, keep, stream);
+  }
   wait_vmem();   // no load may still target LDS when the wave leaves
 #if EFQ_PHASE_STAMPS
-  if (g_stamps && blockIdx.x < kStampBlocks && (threadIdx.x & 255) == 0) {
+  if (kPair && g_stamps && blockIdx.x < kStampBlocks && (threadIdx.x & 255) == 0) {
+    const int group = wave >> 2;
     const unsigned long long* src =
         (const unsigned long long*)(smem + Sm::kStampOff) + group * kStampSlots;
     unsigned long long* dst = g_stamps + ((long)blockIdx.x * 2 + group) * kStampSlots;
@@ -1587,6 +1728,24 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
       }
     }
   }
+}
+
+template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8>
+__global__ __attribute__((amdgpu_flat_work_group_size(kPPThreads, kPPThreads),
+                          amdgpu_waves_per_eu(2, 2))) void
+attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
+               const uint8_t* __restrict__ vhat, float* __restrict__ out, AttnArgs a) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  attn_body<kPPWaves, D, KIND, CAUSAL, DUMP, Q8>(q, k, vhat, out, a, smem);
+}
+
+template <int D, int KIND, bool CAUSAL, bool Q8>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * kHWaves, 64 * kHWaves),
+                          amdgpu_waves_per_eu(2, 2))) void
+attn_half_kernel(const void* __restrict__ q, const void* __restrict__ k,
+                 const uint8_t* __restrict__ vhat, float* __restrict__ out, AttnArgs a) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  attn_body<kHWaves, D, KIND, CAUSAL, false, Q8>(q, k, vhat, out, a, smem);
 }
 
 // ------------------------------------------ standalone probability stage
@@ -1799,6 +1958,7 @@ __global__ __launch_bounds__(256) void rho_final_kernel(const double* __restrict
 // ================================================================ host side
 constexpr int kQTile = kPPBr;   // queries per workgroup of the launched kernel
 constexpr int kMaxDevices = 64; // device indices the library accepts
+constexpr int kCUs = 8 * kXcdCUs;
 
 thread_local char g_msg[512] = "ok";
 
@@ -1892,7 +2052,7 @@ int launch_vquant(const void* v, const efq_shape* s, void* vhat, hipStream_t st)
   return EFQ_OK;
 }
 
-template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8>
+template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8, bool HALF>
 hipError_t launch_attn_t(const void* q, const void* k, const void* vhat, float* out,
                          const AttnArgs& a, hipStream_t st, unsigned grid) {
   // more dynamic LDS than the default limit: raised once per kernel and
@@ -1903,25 +2063,27 @@ hipError_t launch_attn_t(const void* q, const void* k, const void* vhat, float* 
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  std::call_once(once[dev], [dev]() {
-    set_err[dev] = hipFuncSetAttribute((const void*)attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       SmemPP<D, Q8>::kTotal);
+  constexpr int lds = HALF ? SmemH<D, Q8>::kTotal : SmemPP<D, Q8>::kTotal;
+  constexpr int threads = HALF ? 64 * kHWaves : kPPThreads;
+  void (*kernel)(const void*, const void*, const uint8_t*, float*, AttnArgs);
+  if constexpr (HALF) kernel = attn_half_kernel<D, KIND, CAUSAL, Q8>;
+  else kernel = attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8>;
+  std::call_once(once[dev], [dev, kernel]() {
+    set_err[dev] = hipFuncSetAttribute((const void*)kernel,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   });
   if (set_err[dev] != hipSuccess) return set_err[dev];
-  constexpr int lds = SmemPP<D, Q8>::kTotal;
-  hipLaunchKernelGGL((attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8>), dim3(grid), dim3(kPPThreads),
-                     lds, st, q, k, (const uint8_t*)vhat, out, a);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, st, q, k, (const uint8_t*)vhat, out, a);
   return hipGetLastError();
 }
 
-template <int D, bool DUMP, bool Q8>
+template <int D, bool DUMP, bool Q8, bool HALF>
 hipError_t launch_attn_d(int kind, bool causal, const void* q, const void* k, const void* vhat,
                          float* out, const AttnArgs& a, hipStream_t st, unsigned grid) {
-#define EFQ_CASE(KIND)                                                                    \
-  case KIND:                                                                              \
-    return causal ? launch_attn_t<D, KIND, true, DUMP, Q8>(q, k, vhat, out, a, st, grid)  \
-                  : launch_attn_t<D, KIND, false, DUMP, Q8>(q, k, vhat, out, a, st, grid);
+#define EFQ_CASE(KIND)                                                                          \
+  case KIND:                                                                                    \
+    return causal ? launch_attn_t<D, KIND, true, DUMP, Q8, HALF>(q, k, vhat, out, a, st, grid)  \
+                  : launch_attn_t<D, KIND, false, DUMP, Q8, HALF>(q, k, vhat, out, a, st, grid);
   switch (kind) {
     EFQ_CASE(EFQ_PGEN_EFQ)
     EFQ_CASE(EFQ_PGEN_EXPQ)
@@ -1930,10 +2092,12 @@ hipError_t launch_attn_d(int kind, bool causal, const void* q, const void* k, co
     default:
       break;
   }
-  if constexpr (!DUMP) {
-    if (kind == EFQ_PGEN_NOOP)
-      return causal ? launch_attn_t<D, EFQ_PGEN_NOOP, true, false, Q8>(q, k, vhat, out, a, st, grid)
-                    : launch_attn_t<D, EFQ_PGEN_NOOP, false, false, Q8>(q, k, vhat, out, a, st, grid);
+  if constexpr (!DUMP && !HALF) {
+    switch (kind) {
+      EFQ_CASE(EFQ_PGEN_NOOP)
+      default:
+        break;
+    }
   }
 #undef EFQ_CASE
   return hipErrorInvalidValue;
@@ -1970,6 +2134,28 @@ int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st
   return EFQ_OK;
 }
 
+// Whether the half-workgroup kernel takes a shape.  Timed side by side
+// (eight waves / half, us, EFQ unless noted):
+//  - no more eight-wave workgroups than CUs: the half workgroups spread over
+//    idle CUs or finish early ones (one prompt of 1500 / 2048 tokens, 32 heads
+//    32.8 / 28.8 and 43.8 / 38.4; 64 sequences' single queries against 4096 keys
+//    602 / 375, where seven of the eight waves have no query);
+//  - few keys: loads and stores around the tiles weigh most (32760 x 128 / 512 /
+//    1024 keys, 24 heads: 196 / 166, 276 / 263, 396 / 406; 8 prompts of 1024
+//    tokens 90.8 / 84.0, of 2048 277 / 288);
+//  - MXFP8 Q K^T and causal: a tile reads half the K bytes, so the doubled
+//    reads cost little and the even spread of the causal lengths wins (4096
+//    83.9 / 80.1, 6000 168.9 / 163.9, but 16384 1021 / 1060).
+// Elsewhere the eight-wave kernel is as fast or faster (4096 tokens causal
+// 107.5 / 111.3, 7000 x 7000 24 heads 415 / 449).
+bool use_half(const efq_shape* s, int causal, bool q8) {
+  const long wg8 = (long)s->batch * s->heads_q * ((s->seq_q + kQTile - 1) / kQTile);
+  if (s->seq_q <= kQTile / 2) return true;   // at most half of the waves have queries
+  if (s->seq_k <= (causal ? 1024 : 768)) return true;
+  if (causal && q8 && s->seq_k <= 6144) return true;
+  return causal ? wg8 <= kCUs : s->seq_k <= 1536 && wg8 <= 2 * kCUs;
+}
+
 // q8: q and k are the MXFP8 buffers Q^ and K^ of this shape.
 int launch_attn(const void* q, const void* k, const void* vhat, float scale, int causal, int kind,
                 efq_params p, float* out, const efq_shape* s, hipStream_t st, uint8_t* p_codes,
@@ -1982,7 +2168,10 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
   a.Hkv = s->heads_kv;
   a.nb = (int)padded_blocks(s->seq_k);
   a.scale_off = vhat_scale_offset(s);
-  a.nqt = (s->seq_q + kQTile - 1) / kQTile;
+  const bool dump = p_codes != nullptr;
+  const bool half = !dump && kind != EFQ_PGEN_NOOP && use_half(s, causal, q8);
+  const int br = half ? kWaveQ * kHWaves : kQTile;
+  a.nqt = (s->seq_q + br - 1) / br;
   a.scale = scale;
   a.tau = p.tau;
   a.h = p.h;
@@ -1993,28 +2182,22 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
   a.nblk = (s->seq_k + 31) / 32;
   const long total = (long)a.B * a.Hq * a.nqt;
   a.xcd_remap = (total % 8 == 0) ? 1 : 0;
+  a.spread = half && causal && total <= 2 * kCUs && (long)a.B * a.Hq % 8 == 0 ? 1 : 0;
   a.sq_pad = (int)pad64(s->seq_q);
   a.sk_pad = (int)pad64(s->seq_k);
   a.q8_soff = q8_scale_offset(qhat_rows(s), s->head_dim);
   a.k8_soff = q8_scale_offset(khat_rows(s), s->head_dim);
-  const bool dump = p_codes != nullptr;
   const unsigned g = (unsigned)total;
+  auto launch = [&](auto d, auto is_q8) {
+    constexpr int D = decltype(d)::value;
+    constexpr bool Q8 = decltype(is_q8)::value;
+    if (dump) return launch_attn_d<D, true, Q8, false>(kind, causal, q, k, vhat, out, a, st, g);
+    if (half) return launch_attn_d<D, false, Q8, true>(kind, causal, q, k, vhat, out, a, st, g);
+    return launch_attn_d<D, false, Q8, false>(kind, causal, q, k, vhat, out, a, st, g);
+  };
   hipError_t e;
-  if (s->head_dim == 64) {
-    if (q8)
-      e = dump ? launch_attn_d<64, true, true>(kind, causal, q, k, vhat, out, a, st, g)
-               : launch_attn_d<64, false, true>(kind, causal, q, k, vhat, out, a, st, g);
-    else
-      e = dump ? launch_attn_d<64, true, false>(kind, causal, q, k, vhat, out, a, st, g)
-               : launch_attn_d<64, false, false>(kind, causal, q, k, vhat, out, a, st, g);
-  } else {
-    if (q8)
-      e = dump ? launch_attn_d<128, true, true>(kind, causal, q, k, vhat, out, a, st, g)
-               : launch_attn_d<128, false, true>(kind, causal, q, k, vhat, out, a, st, g);
-    else
-      e = dump ? launch_attn_d<128, true, false>(kind, causal, q, k, vhat, out, a, st, g)
-               : launch_attn_d<128, false, false>(kind, causal, q, k, vhat, out, a, st, g);
-  }
+  if (s->head_dim == 64) e = q8 ? launch(IC<64>{}, std::true_type{}) : launch(IC<64>{}, std::false_type{});
+  else e = q8 ? launch(IC<128>{}, std::true_type{}) : launch(IC<128>{}, std::false_type{});
   if (e != hipSuccess) return fail(EFQ_EHIP, "attention launch: %s", hipGetErrorString(e));
   return EFQ_OK;
 }
