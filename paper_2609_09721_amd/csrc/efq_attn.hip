@@ -11,12 +11,15 @@
 //                      on the block-scaled FP4 MFMA, the denominator P~ 1
 //                      from the same operand; two wave groups alternate
 //                      matrix-core and VALU phases.
+//   attn_half_kernel   the same tile code in workgroups of four waves, two on
+//                      a CU, for short or small grids.
 //   pgen_kernel        the probability stage alone on given shifted scores.
 //   pgen_bench_kernel  register-resident throughput probe of that stage.
 //   clock_probe_kernel shader clock under a matrix-core load (diagnostic).
-//   rho_partial_kernel, rho_final_kernel
-//                      the relative Frobenius error of Alg. 3's calibration
-//                      objective, in fp64 with a fixed reduction order.
+//   attn_rho_kernel, rho_final_kernel
+//                      the attention of many calibration candidates and the
+//                      relative Frobenius error of Alg. 3's objective, in
+//                      fp64 with a fixed reduction order.
 //   fill_zero_kernel   zero fill of the dump buffers (blocks never reached).
 //
 // Register layout (v_mfma_f32_32x32x16_bf16, verified on gfx950): lane L of a
@@ -29,6 +32,7 @@
 // scale per lane) of v_mfma_scale_f32_32x32x64_f8f6f4 in FP4 mode.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdint>
@@ -1516,11 +1520,14 @@ __device__ __forceinline__ void half_schedule(PPWave<D, KIND, false, Q8, false>&
 // or NW = 4 in the half workgroup's.
 // Q8: q and k are the MXFP8 buffers Q^ and K^ (E4M3 codes, then E8M0 scales
 // at a.q8_soff / a.k8_soff, [batch][head][padded seq] rows), else bf16 BSHD.
-template <int NW, int D, int KIND, bool CAUSAL, bool DUMP, bool Q8>
+// RHO: instead of storing O, the sums of (O - o_ref)^2 and o_ref^2 over the
+// workgroup's outputs, in fp64 and a fixed order, go to rho[0] and rho[1].
+template <int NW, int D, int KIND, bool CAUSAL, bool DUMP, bool Q8, bool RHO = false>
 __device__ __forceinline__ void attn_body(const void* __restrict__ q, const void* __restrict__ k,
                                           const uint8_t* __restrict__ vhat,
                                           float* __restrict__ out, const AttnArgs& a,
-                                          uint8_t* smem) {
+                                          uint8_t* smem, const float* __restrict__ o_ref = nullptr,
+                                          double* __restrict__ rho = nullptr) {
   constexpr bool kPair = NW == kPPWaves;     // the ping-pong schedule
   constexpr int kBr = kWaveQ * NW;           // queries per workgroup
   constexpr int KK = D / 16;
@@ -1708,7 +1715,43 @@ __device__ __forceinline__ void attn_body(const void* __restrict__ q, const void
   // residual range [log 3/4, log 3/2) can produce; the row is then 0.
   const float l = w.lacc[0];
   const float rl = l > 0.0f ? 1.0f / l : 0.0f;
-  if (w.my_q < a.Sq) {
+  if constexpr (RHO) {
+    double d2 = 0.0, r2 = 0.0;
+    if (w.my_q < a.Sq) {
+      const float* rp = o_ref + (((long)b * a.Sq + w.my_q) * a.Hq + hq) * D;
+#pragma unroll
+      for (int s = 0; s < NS; ++s) {
+#pragma unroll
+        for (int r4 = 0; r4 < 4; ++r4) {
+          const f32x4 v = *(const f32x4*)(rp + s * 32 + 8 * r4 + 4 * w.half);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const double o = w.oacc[s][4 * r4 + i] * rl, d = o - (double)v[i];
+            d2 += d * d;
+            r2 += (double)v[i] * (double)v[i];
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int x = 32; x > 0; x >>= 1) {
+      d2 += __shfl_xor(d2, x);
+      r2 += __shfl_xor(r2, x);
+    }
+    double* const red = (double*)smem;
+    __syncthreads();   // every wave is done with the rings
+    if (w.lane == 0) {
+      red[2 * wave] = d2;
+      red[2 * wave + 1] = r2;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+      double t = 0.0;
+#pragma unroll
+      for (int i = 0; i < NW; ++i) t += red[2 * i + threadIdx.x];
+      rho[threadIdx.x] = t;
+    }
+  } else if (w.my_q < a.Sq) {
     float* op = out + (((long)b * a.Sq + w.my_q) * a.Hq + hq) * D;
 #pragma unroll
     for (int s = 0; s < NS; ++s) {
@@ -1898,44 +1941,41 @@ __global__ void fill_zero_kernel(uint8_t* __restrict__ p, size_t n) {
 }
 
 // ------------------------------------------------ calibration objective
-// rho(tau, h) = ||O~ - O_ref||_F / ||O_ref||_F (Sec. III-C, Alg. 3): sums of
-// squares in fp64, reduced in a fixed order (per-block partials, then one
-// block), so repeated runs give identical values.
-constexpr int kRhoBlocks = 1024;
+// rho(tau, h) = ||O~ - O_ref||_F / ||O_ref||_F (Sec. III-C, Alg. 3).  One
+// launch runs the EFQ attention for up to kRhoCand candidate pairs (grid y)
+// and keeps only the sums of squares, in fp64: a candidate's output is never
+// stored and read back, and the candidates together fill the chip, which one
+// short calibration prompt does not.  The sums are reduced in a fixed order
+// (lanes, waves, then rho_final_kernel over the workgroups), so repeated
+// runs give identical values.  Matrix-core bound, as the attention itself:
+// 16 candidates on 1024 tokens (32/8 heads, D 128) took 16 x (28.8 us
+// attention + 8.0 us for the sums over the stored output + 2.8 us to reduce
+// them); a whole call 724 us, now 187.
+constexpr int kRhoCand = 64;
+struct RhoCand {
+  float tau[kRhoCand], h[kRhoCand];
+};
 
-__global__ __launch_bounds__(256) void rho_partial_kernel(const float* __restrict__ o,
-                                                          const float* __restrict__ r, long n,
-                                                          double* __restrict__ part) {
-  double d2 = 0.0, r2 = 0.0;
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) {
-    const double a = o[i], b = r[i];
-    d2 += (a - b) * (a - b);
-    r2 += b * b;
-  }
-  __shared__ double s1[256], s2[256];
-  s1[threadIdx.x] = d2;
-  s2[threadIdx.x] = r2;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) {
-      s1[threadIdx.x] += s1[threadIdx.x + w];
-      s2[threadIdx.x] += s2[threadIdx.x + w];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    part[2 * blockIdx.x] = s1[0];
-    part[2 * blockIdx.x + 1] = s2[0];
-  }
+template <int NW, int D, bool CAUSAL>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * NW, 64 * NW), amdgpu_waves_per_eu(2, 2))) void
+attn_rho_kernel(const void* __restrict__ q, const void* __restrict__ k,
+                const uint8_t* __restrict__ vhat, const float* __restrict__ o_ref, AttnArgs a,
+                RhoCand cand, double* __restrict__ part) {
+  extern __shared__ __align__(16) uint8_t smem[];
+  a.tau = cand.tau[blockIdx.y];
+  a.h = cand.h[blockIdx.y];
+  attn_body<NW, D, EFQ_PGEN_EFQ, CAUSAL, false, false, true>(
+      q, k, vhat, nullptr, a, smem, o_ref, part + 2 * ((long)blockIdx.y * gridDim.x + blockIdx.x));
 }
 
-// One block: the kRhoBlocks partial pairs -> res[0] = sum (O~ - O_ref)^2,
-// res[1] = sum O_ref^2.
-__global__ __launch_bounds__(256) void rho_final_kernel(const double* __restrict__ part,
+// One block per candidate: its n partial pairs -> res[2 c] = sum (O~ -
+// O_ref)^2, res[2 c + 1] = sum O_ref^2.
+__global__ __launch_bounds__(256) void rho_final_kernel(const double* __restrict__ part, long n,
                                                         double* __restrict__ res) {
   __shared__ double s1[256], s2[256];
+  part += 2 * n * blockIdx.x;
   double a = 0.0, b = 0.0;
-  for (int i = threadIdx.x; i < kRhoBlocks; i += 256) {
+  for (long i = threadIdx.x; i < n; i += 256) {
     a += part[2 * i];
     b += part[2 * i + 1];
   }
@@ -1950,8 +1990,8 @@ __global__ __launch_bounds__(256) void rho_final_kernel(const double* __restrict
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    res[0] = s1[0];
-    res[1] = s2[0];
+    res[2 * blockIdx.x] = s1[0];
+    res[2 * blockIdx.x + 1] = s2[0];
   }
 }
 
@@ -2052,29 +2092,43 @@ int launch_vquant(const void* v, const efq_shape* s, void* vhat, hipStream_t st)
   return EFQ_OK;
 }
 
-template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8, bool HALF>
-hipError_t launch_attn_t(const void* q, const void* k, const void* vhat, float* out,
-                         const AttnArgs& a, hipStream_t st, unsigned grid) {
-  // more dynamic LDS than the default limit: raised once per kernel and
-  // device (check_device has bounded the device index)
+template <auto F>
+struct KernelPtr {
+  static constexpr auto value = F;
+};
+
+// More dynamic LDS than the default limit for KERNEL: raised once per device
+// (check_device has bounded the device index).
+template <auto KERNEL>
+hipError_t raise_lds(int lds) {
   static std::once_flag once[kMaxDevices];
   static hipError_t set_err[kMaxDevices];
   int dev = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return e;
   if (dev < 0 || dev >= kMaxDevices) return hipErrorInvalidDevice;
-  constexpr int lds = HALF ? SmemH<D, Q8>::kTotal : SmemPP<D, Q8>::kTotal;
-  constexpr int threads = HALF ? 64 * kHWaves : kPPThreads;
-  void (*kernel)(const void*, const void*, const uint8_t*, float*, AttnArgs);
-  if constexpr (HALF) kernel = attn_half_kernel<D, KIND, CAUSAL, Q8>;
-  else kernel = attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8>;
-  std::call_once(once[dev], [dev, kernel]() {
-    set_err[dev] = hipFuncSetAttribute((const void*)kernel,
+  std::call_once(once[dev], [dev, lds]() {
+    set_err[dev] = hipFuncSetAttribute((const void*)KERNEL,
                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   });
-  if (set_err[dev] != hipSuccess) return set_err[dev];
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), lds, st, q, k, (const uint8_t*)vhat, out, a);
-  return hipGetLastError();
+  return set_err[dev];
+}
+
+template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8, bool HALF>
+hipError_t launch_attn_t(const void* q, const void* k, const void* vhat, float* out,
+                         const AttnArgs& a, hipStream_t st, unsigned grid) {
+  auto launch = [&](auto kernel, int threads, int lds) {
+    const hipError_t e = raise_lds<decltype(kernel)::value>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(decltype(kernel)::value, dim3(grid), dim3(threads), lds, st, q, k,
+                       (const uint8_t*)vhat, out, a);
+    return hipGetLastError();
+  };
+  if constexpr (HALF)
+    return launch(KernelPtr<attn_half_kernel<D, KIND, CAUSAL, Q8>>{}, 64 * kHWaves, SmemH<D, Q8>::kTotal);
+  else
+    return launch(KernelPtr<attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8>>{}, kPPThreads,
+                  SmemPP<D, Q8>::kTotal);
 }
 
 template <int D, bool DUMP, bool Q8, bool HALF>
@@ -2149,6 +2203,9 @@ int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st
 // Elsewhere the eight-wave kernel is as fast or faster (4096 tokens causal
 // 107.5 / 111.3, 7000 x 7000 24 heads 415 / 449).
 bool use_half(const efq_shape* s, int causal, bool q8) {
+#if EFQ_PHASE_STAMPS
+  return false;   // the stamped build records the eight-wave kernel
+#endif
   const long wg8 = (long)s->batch * s->heads_q * ((s->seq_q + kQTile - 1) / kQTile);
   if (s->seq_q <= kQTile / 2) return true;   // at most half of the waves have queries
   if (s->seq_k <= (causal ? 1024 : 768)) return true;
@@ -2156,10 +2213,15 @@ bool use_half(const efq_shape* s, int causal, bool q8) {
   return causal ? wg8 <= kCUs : s->seq_k <= 1536 && wg8 <= 2 * kCUs;
 }
 
-// q8: q and k are the MXFP8 buffers Q^ and K^ of this shape.
-int launch_attn(const void* q, const void* k, const void* vhat, float scale, int causal, int kind,
-                efq_params p, float* out, const efq_shape* s, hipStream_t st, uint8_t* p_codes,
-                uint8_t* p_e8m0, float* row_m, float* row_l, bool q8 = false) {
+// The calibration runs many candidates in one launch, so the grid is never
+// short; the half workgroups win where they do for a large grid (few keys).
+bool rho_half(const efq_shape* s, int causal) {
+  return s->seq_q <= kQTile / 2 || s->seq_k <= (causal ? 1024 : 768);
+}
+
+// Arguments and grid size of an attention launch (half: the half-workgroup
+// kernel), without the dump buffers.
+AttnArgs attn_args(const efq_shape* s, float scale, int causal, efq_params p, bool half, unsigned& grid) {
   AttnArgs a;
   a.B = s->batch;
   a.Sq = s->seq_q;
@@ -2168,17 +2230,13 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
   a.Hkv = s->heads_kv;
   a.nb = (int)padded_blocks(s->seq_k);
   a.scale_off = vhat_scale_offset(s);
-  const bool dump = p_codes != nullptr;
-  const bool half = !dump && kind != EFQ_PGEN_NOOP && use_half(s, causal, q8);
   const int br = half ? kWaveQ * kHWaves : kQTile;
   a.nqt = (s->seq_q + br - 1) / br;
   a.scale = scale;
   a.tau = p.tau;
   a.h = p.h;
-  a.p_codes = p_codes;
-  a.p_e8m0 = p_e8m0;
-  a.row_m = row_m;
-  a.row_l = row_l;
+  a.p_codes = a.p_e8m0 = nullptr;
+  a.row_m = a.row_l = nullptr;
   a.nblk = (s->seq_k + 31) / 32;
   const long total = (long)a.B * a.Hq * a.nqt;
   a.xcd_remap = (total % 8 == 0) ? 1 : 0;
@@ -2187,7 +2245,22 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
   a.sk_pad = (int)pad64(s->seq_k);
   a.q8_soff = q8_scale_offset(qhat_rows(s), s->head_dim);
   a.k8_soff = q8_scale_offset(khat_rows(s), s->head_dim);
-  const unsigned g = (unsigned)total;
+  grid = (unsigned)total;
+  return a;
+}
+
+// q8: q and k are the MXFP8 buffers Q^ and K^ of this shape.
+int launch_attn(const void* q, const void* k, const void* vhat, float scale, int causal, int kind,
+                efq_params p, float* out, const efq_shape* s, hipStream_t st, uint8_t* p_codes,
+                uint8_t* p_e8m0, float* row_m, float* row_l, bool q8 = false) {
+  const bool dump = p_codes != nullptr;
+  const bool half = !dump && kind != EFQ_PGEN_NOOP && use_half(s, causal, q8);
+  unsigned g;
+  AttnArgs a = attn_args(s, scale, causal, p, half, g);
+  a.p_codes = p_codes;
+  a.p_e8m0 = p_e8m0;
+  a.row_m = row_m;
+  a.row_l = row_l;
   auto launch = [&](auto d, auto is_q8) {
     constexpr int D = decltype(d)::value;
     constexpr bool Q8 = decltype(is_q8)::value;
@@ -2218,6 +2291,45 @@ int check_params(efq_params p) {
 
 int check_scale(float scale) {
   if (!std::isfinite(scale) || !(scale > 0.0f)) return fail(EFQ_EINVAL, "scale must be finite and > 0");
+  return EFQ_OK;
+}
+
+// The objective sums of candidates c0 .. c0 + n - 1 (at most kRhoCand); part:
+// n x grid pairs of doubles, res: n pairs.
+int launch_rho(const void* q, const void* k, const void* vhat, float scale, int causal,
+               const float* o_ref, const efq_shape* s, const float* taus, const float* hs, int nh,
+               int c0, int n, double* part, double* res, hipStream_t st) {
+  const bool half = rho_half(s, causal);
+  unsigned g;
+  AttnArgs a = attn_args(s, scale, causal, efq_params{0.0f, 1.0f}, half, g);
+  a.spread = 0;   // several candidates are more than the chip holds at once
+  RhoCand cand;
+  for (int i = 0; i < kRhoCand; ++i) {
+    const int c = c0 + (i < n ? i : 0);
+    cand.tau[i] = taus[c / nh];
+    cand.h[i] = hs[c % nh];
+  }
+  auto launch = [&](auto kernel, int threads, int lds) {
+    const hipError_t e = raise_lds<decltype(kernel)::value>(lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(decltype(kernel)::value, dim3(g, n), dim3(threads), lds, st, q, k,
+                       (const uint8_t*)vhat, o_ref, a, cand, part);
+    return hipGetLastError();
+  };
+  auto pick = [&](auto d, auto c) {
+    constexpr int D = decltype(d)::value;
+    constexpr bool C = decltype(c)::value;
+    return half ? launch(KernelPtr<attn_rho_kernel<kHWaves, D, C>>{}, 64 * kHWaves, SmemH<D>::kTotal)
+                : launch(KernelPtr<attn_rho_kernel<kPPWaves, D, C>>{}, kPPThreads, SmemPP<D>::kTotal);
+  };
+  hipError_t e;
+  if (s->head_dim == 64) e = causal ? pick(IC<64>{}, std::true_type{}) : pick(IC<64>{}, std::false_type{});
+  else e = causal ? pick(IC<128>{}, std::true_type{}) : pick(IC<128>{}, std::false_type{});
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(rho_final_kernel, dim3(n), dim3(256), 0, st, part, (long)g, res);
+    e = hipGetLastError();
+  }
+  if (e != hipSuccess) return fail(EFQ_EHIP, "calibration launch: %s", hipGetErrorString(e));
   return EFQ_OK;
 }
 
@@ -2516,14 +2628,16 @@ int efq_attn_fwd_lowbit_ex(const void* q, const void* k, const void* v, float sc
   return rc;
 }
 
-// Workspace of efq_calibrate: V~, one output, the reduction partials and
-// one result pair per candidate, each 256-byte aligned.
+// Workspace of efq_calibrate: V~, the partial sums (as large as one output
+// and kRhoPad pairs: room for at least 16 candidates a launch) and one result
+// pair per candidate, each 256-byte aligned.
+constexpr int kRhoPad = 1024;
 static size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 size_t efq_calibrate_workspace_bytes(const efq_shape* s, int ncand) {
   if (!s || ncand < 1 || validate_shape(s, 0) != EFQ_OK) return 0;
   const size_t out = (size_t)s->batch * s->seq_q * s->heads_q * s->head_dim * 4;
-  return align256(vhat_bytes(s)) + align256(out) + align256((size_t)kRhoBlocks * 16) +
+  return align256(vhat_bytes(s)) + align256(out) + align256((size_t)kRhoPad * 16) +
          align256((size_t)ncand * 16);
 }
 
@@ -2555,22 +2669,19 @@ int efq_calibrate(const void* q, const void* k, const void* v, float scale, int 
     if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", need, hipGetErrorString(e));
   }
   uint8_t* vhat = buf;
-  float* out = (float*)(buf + align256(vhat_bytes(s)));
-  const long n = (long)s->batch * s->seq_q * s->heads_q * s->head_dim;
-  double* part = (double*)((uint8_t*)out + align256((size_t)n * 4));
-  double* res = (double*)((uint8_t*)part + align256((size_t)kRhoBlocks * 16));
-  // Alg. 3: every (tau, h), tau outer, on the same inputs and V~
+  double* part = (double*)(buf + align256(vhat_bytes(s)));
+  const size_t room = align256((size_t)s->batch * s->seq_q * s->heads_q * s->head_dim * 4) +
+                      align256((size_t)kRhoPad * 16);
+  double* res = (double*)((uint8_t*)part + room);
+  // Alg. 3: every (tau, h), tau outer, on the same inputs and V~; as many
+  // candidates a launch as the partial sums have room for
+  const int br = rho_half(s, causal) ? kWaveQ * kHWaves : kQTile;
+  const size_t wgs = (size_t)s->batch * s->heads_q * ((s->seq_q + br - 1) / br);
+  const int most = (int)std::min<size_t>(kRhoCand, room / (wgs * 16));
   rc = launch_vquant(v, s, vhat, st);
-  for (int c = 0; c < nc && rc == EFQ_OK; ++c) {
-    const efq_params p{taus[c / nh], hs[c % nh]};
-    rc = launch_attn(q, k, vhat, scale, causal, EFQ_PGEN_EFQ, p, out, s, st, nullptr, nullptr,
-                     nullptr, nullptr);
-    if (rc != EFQ_OK) break;
-    hipLaunchKernelGGL(rho_partial_kernel, dim3(kRhoBlocks), dim3(256), 0, st, out, o_ref, n, part);
-    hipLaunchKernelGGL(rho_final_kernel, dim3(1), dim3(256), 0, st, part, res + 2 * c);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) rc = fail(EFQ_EHIP, "calibration launch: %s", hipGetErrorString(e));
-  }
+  for (int c = 0; c < nc && rc == EFQ_OK; c += most)
+    rc = launch_rho(q, k, vhat, scale, causal, o_ref, s, taus, hs, nh, c, std::min(most, nc - c), part,
+                    res + 2 * c, st);
   std::vector<double> sums((size_t)nc * 2);
   if (rc == EFQ_OK) {
     hipError_t e = hipMemcpyAsync(sums.data(), res, sums.size() * sizeof(double),
