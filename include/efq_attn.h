@@ -126,9 +126,24 @@ int efq_attn_fwd_vhat(const void *q, const void *k, const void *vhat, size_t vha
                       float scale, int causal, int kind, efq_params p, float *out,
                       const efq_shape *s, efq_stream_t stream);
 
-/* Both steps with a caller-owned workspace of at least
- * efq_attn_workspace_bytes(s) bytes (ws may be NULL when ws_bytes == 0: then
- * the library takes a stream-ordered allocation). */
+/* Few queries (seq_q * heads_q / heads_kv <= 128) against many keys run split
+ * over the keys, non-causal only, when there is scratch memory for it.  The
+ * codes, scales and row maxima are those of the unsplit kernels; the output
+ * is the same sums taken in another order (fp32 rounding).
+ * efq_attn_split_bytes: the scratch bytes for this shape with bf16 (qk8 == 0)
+ * or MXFP8 (qk8 != 0) Q K^T, 0 where the split is not used.
+ * efq_attn_fwd_vhat_ws: efq_attn_fwd_vhat with scratch (device, 16-byte
+ * aligned).  Without it (ws NULL, ws_bytes 0) or with less than
+ * efq_attn_split_bytes the unsplit kernels run, as in efq_attn_fwd_vhat. */
+size_t efq_attn_split_bytes(const efq_shape *s, int qk8);
+int efq_attn_fwd_vhat_ws(const void *q, const void *k, const void *vhat, size_t vhat_bytes,
+                         float scale, int causal, int kind, efq_params p, float *out,
+                         const efq_shape *s, void *ws, size_t ws_bytes, efq_stream_t stream);
+
+/* Both steps with a caller-owned workspace of at least efq_vhat_bytes(s)
+ * bytes; efq_attn_workspace_bytes(s) adds efq_attn_split_bytes(s, 0), with
+ * which few queries run split over the keys (ws may be NULL when
+ * ws_bytes == 0: then the library takes a stream-ordered allocation). */
 size_t efq_attn_workspace_bytes(const efq_shape *s);
 int efq_attn_fwd_ex(const void *q, const void *k, const void *v, float scale, int causal,
                     int kind, efq_params p, float *out, const efq_shape *s, void *ws,
@@ -190,6 +205,13 @@ int efq_attn_fwd_qk8(const void *qhat, size_t qhat_bytes, const void *khat, size
                      const void *vhat, size_t vhat_bytes, float scale, int causal, int kind,
                      efq_params p, float *out, const efq_shape *s, efq_stream_t stream);
 
+/* efq_attn_fwd_qk8 with the scratch of efq_attn_split_bytes(s, 1), as
+ * efq_attn_fwd_vhat_ws. */
+int efq_attn_fwd_qk8_ws(const void *qhat, size_t qhat_bytes, const void *khat, size_t khat_bytes,
+                        const void *vhat, size_t vhat_bytes, float scale, int causal, int kind,
+                        efq_params p, float *out, const efq_shape *s, void *ws, size_t ws_bytes,
+                        efq_stream_t stream);
+
 /* efq_attn_fwd_qk8 recording the probability stage, as efq_attn_fwd_dump. */
 int efq_attn_fwd_qk8_dump(const void *qhat, size_t qhat_bytes, const void *khat,
                           size_t khat_bytes, const void *vhat, size_t vhat_bytes, float scale,
@@ -197,10 +219,12 @@ int efq_attn_fwd_qk8_dump(const void *qhat, size_t qhat_bytes, const void *khat,
                           uint8_t *p_codes, uint8_t *p_e8m0, float *row_m, float *row_l,
                           efq_stream_t stream);
 
-/* All three quantisers and the attention with one workspace of at least
- * efq_attn_lowbit_workspace_bytes(s) bytes, 256-byte aligned (Q^, K^ and V~
- * at 256-byte boundaries in that order); ws may be NULL with ws_bytes == 0
- * (one stream-ordered allocation, released on the same stream). */
+/* All three quantisers and the attention with one workspace, 256-byte aligned
+ * (Q^, K^ and V~ at 256-byte boundaries in that order, then, where it fits,
+ * the efq_attn_split_bytes(s, 1) of the key split;
+ * efq_attn_lowbit_workspace_bytes(s) is the whole); ws may be NULL with
+ * ws_bytes == 0 (one stream-ordered allocation, released on the same
+ * stream). */
 size_t efq_attn_lowbit_workspace_bytes(const efq_shape *s);
 int efq_attn_fwd_lowbit_ex(const void *q, const void *k, const void *v, float scale, int causal,
                            int kind, efq_params p, float *out, const efq_shape *s, void *ws,

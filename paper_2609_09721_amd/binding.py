@@ -59,6 +59,8 @@ SIGNATURES = {
     "efq_attn_workspace_bytes": ([SP], SZ),
     "efq_quant_v_mxfp4": ([P, SP, P, SZ, P], I),
     "efq_attn_fwd_vhat": ([P, P, P, SZ, F, I, I, Params, P, SP, P], I),
+    "efq_attn_split_bytes": ([SP, I], SZ),
+    "efq_attn_fwd_vhat_ws": ([P, P, P, SZ, F, I, I, Params, P, SP, P, SZ, P], I),
     "efq_attn_fwd_ex": ([P, P, P, F, I, I, Params, P, SP, P, SZ, P], I),
     "efq_attn_fwd": ([P, P, P, F, I, P, SP, P], I),
     "efq_attn_fwd_noalloc": ([P, P, P, F, I, I, Params, P, SP, P], I),
@@ -75,6 +77,7 @@ SIGNATURES = {
     "efq_khat_scale_offset": ([SP], SZ),
     "efq_quant_qk_mxfp8": ([P, P, SP, P, SZ, P, SZ, P], I),
     "efq_attn_fwd_qk8": ([P, SZ, P, SZ, P, SZ, F, I, I, Params, P, SP, P], I),
+    "efq_attn_fwd_qk8_ws": ([P, SZ, P, SZ, P, SZ, F, I, I, Params, P, SP, P, SZ, P], I),
     "efq_attn_fwd_qk8_dump": ([P, SZ, P, SZ, P, SZ, F, I, I, Params, P, SP, P, P, P, P, P], I),
     "efq_attn_lowbit_workspace_bytes": ([SP], SZ),
     "efq_attn_fwd_lowbit_ex": ([P, P, P, F, I, I, Params, P, SP, P, SZ, P], I),
@@ -134,6 +137,23 @@ def _bf16(t: torch.Tensor, name: str):
         raise ValueError(f"{name} must be a contiguous bf16 CUDA tensor")
 
 
+def _scratch(nbytes: int, device, stream=None) -> Optional[torch.Tensor]:
+    """Scratch of one call from torch's allocator, in the memory pool of the
+    stream that uses it (so it is reused only after that work), or None."""
+    if nbytes == 0:
+        return None
+    if stream is None:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    with torch.cuda.stream(stream):
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _split_scratch(shape: Shape, causal, qk8: bool, device, stream):
+    """(scratch or None, bytes) of the key split that few queries run by."""
+    n = 0 if causal else int(lib().efq_attn_split_bytes(ctypes.byref(shape), int(qk8)))
+    return _scratch(n, device, stream), n
+
+
 def vhat_bytes(shape: Shape) -> int:
     return int(lib().efq_vhat_bytes(ctypes.byref(shape)))
 
@@ -166,9 +186,10 @@ def attn_fwd_vhat(q, k, vhat, scale: Optional[float] = None, causal: bool = Fals
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    _check(lib().efq_attn_fwd_vhat(_ptr(q), _ptr(k), _ptr(vhat), vhat.numel(), float(scale),
-                                   int(causal), kind, _params(kind, params), _ptr(out),
-                                   ctypes.byref(sh), _stream(stream)))
+    ws, ws_n = _split_scratch(sh, causal, False, q.device, stream)
+    _check(lib().efq_attn_fwd_vhat_ws(_ptr(q), _ptr(k), _ptr(vhat), vhat.numel(), float(scale),
+                                      int(causal), kind, _params(kind, params), _ptr(out),
+                                      ctypes.byref(sh), _ptr(ws), ws_n, _stream(stream)))
     return out
 
 
@@ -273,10 +294,11 @@ def attn_fwd_qk8(qhat, khat, vhat, shape: Shape, scale: Optional[float] = None,
     if out is None:
         out = torch.empty((shape.batch, shape.seq_q, shape.heads_q, shape.head_dim),
                           dtype=torch.float32, device=qhat.device)
-    _check(lib().efq_attn_fwd_qk8(_ptr(qhat), qhat.numel(), _ptr(khat), khat.numel(), _ptr(vhat),
-                                  vhat.numel(), float(scale), int(causal), kind,
-                                  _params(kind, params), _ptr(out), ctypes.byref(shape),
-                                  _stream(stream)))
+    ws, ws_n = _split_scratch(shape, causal, True, qhat.device, stream)
+    _check(lib().efq_attn_fwd_qk8_ws(_ptr(qhat), qhat.numel(), _ptr(khat), khat.numel(), _ptr(vhat),
+                                     vhat.numel(), float(scale), int(causal), kind,
+                                     _params(kind, params), _ptr(out), ctypes.byref(shape), _ptr(ws),
+                                     ws_n, _stream(stream)))
     return out
 
 

@@ -10,15 +10,15 @@
 //                      exp-then-quantize for the baselines), O^T += V~^T P~^T
 //                      on the block-scaled FP4 MFMA, the denominator P~ 1
 //                      from the same operand; two wave groups alternate
-//                      matrix-core and VALU phases.
-//   attn_half_kernel   the same tile code in workgroups of four waves, two on
-//                      a CU, for short or small grids.
+//                      matrix-core and VALU phases; with NW = 4, workgroups
+//                      of four waves, two on a CU, for short or small grids;
+//                      with RHO, calibration candidates (below).
+//   split_max_kernel, split_attn_kernel, split_merge_kernel
+//                      few queries against many keys, split over the keys.
 //   pgen_kernel        the probability stage alone on given shifted scores.
 //   pgen_bench_kernel  register-resident throughput probe of that stage.
 //   clock_probe_kernel shader clock under a matrix-core load (diagnostic).
-//   attn_rho_kernel, rho_final_kernel
-//                      the attention of many calibration candidates and the
-//                      relative Frobenius error of Alg. 3's objective, in
+//   rho_final_kernel   the relative Frobenius error of Alg. 3's objective, in
 //                      fp64 with a fixed reduction order.
 //   fill_zero_kernel   zero fill of the dump buffers (blocks never reached).
 //
@@ -143,8 +143,7 @@ __host__ __device__ constexpr int key_nibble(int t) {
 // The stage is split into pieces so the fused kernel can interleave them
 // with the matrix-core work of the next tile:
 //   pg_max     partial block maxima of the lane's 32 scores
-//   pg_rowmax  the tile's row maximum
-//   pg_params  the change of the row maximum, and the per-block parameters (Alg. 1:
+//   pg_params  row maximum, its change, and the per-block parameters (Alg. 1:
 //              M_b, k_b, and the affine bias; or the exp-then-quantize scale)
 //   pg_alpha   alpha from the change (the fused kernel forms it only when
 //              some row maximum of the wave moved)
@@ -193,29 +192,9 @@ __device__ __forceinline__ void pg_max(const f32x16& s0, const f32x16& s1, float
 template <int KIND>
 constexpr bool is_expq() { return KIND == EFQ_PGEN_EXPQ || KIND == EFQ_PGEN_EXPQ6; }
 
-// The maximum of a query's 64 scores (rowmax S^j, in the stage's units) and
-// bs, that of the lane's own block.
+// Returns whether some row maximum of the wave moved (wave-uniform).
 template <int KIND>
-__device__ __forceinline__ float pg_rowmax(float pm0, float pm1, const PgenArgs& pa, float& bs) {
-  if constexpr (KIND == EFQ_PGEN_NOOP) {
-    return bs = 0.0f;
-  } else {
-    const float unit = is_expq<KIND>() ? pa.l2s : pa.scale;
-    swap32f(pm0, pm1);                          // lower: (own, partner) block 0; upper: block 1
-    const float bmine = fmax_swapped(pm0, pm1);  // raw maximum of the lane's own block
-    // the lane's block maximum in score units; rounding is monotone, so the
-    // row maximum of the products is the product of the raw row maximum
-    bs = bmine * unit;
-    float t0 = bs, t1 = bs;
-    swap32f(t0, t1);                            // (block 0 max, block 1 max) in every lane
-    return fmax_swapped(t0, t1);                // rowmax S^j
-  }
-}
-
-// The block parameters, with the new running maximum mnew.  Returns whether
-// some row maximum of the wave moved (wave-uniform).
-template <int KIND>
-__device__ __forceinline__ bool pg_params(float bs, float mnew, float& m, const PgenArgs& pa,
+__device__ __forceinline__ bool pg_params(float pm0, float pm1, float& m, const PgenArgs& pa,
                                           PgenState& st) {
   bool moved = false;
   if constexpr (KIND == EFQ_PGEN_NOOP) {
@@ -224,6 +203,18 @@ __device__ __forceinline__ bool pg_params(float bs, float mnew, float& m, const 
     st.w[0] = st.w[1] = st.w[2] = st.w[3] = 0x22222222u;
     return moved;
   } else {
+    constexpr bool LOG2 = is_expq<KIND>();
+    const float unit = LOG2 ? pa.l2s : pa.scale;
+    swap32f(pm0, pm1);                          // lower: (own, partner) block 0; upper: block 1
+    const float bmine = fmax_swapped(pm0, pm1);  // raw maximum of the lane's own block
+    // the lane's block maximum in score units; rounding is monotone, so the
+    // row maximum of the products is the product of the raw row maximum
+    const float bs = bmine * unit;
+    float t0 = bs, t1 = bs;
+    swap32f(t0, t1);                            // (block 0 max, block 1 max) in every lane
+    const float mt = fmax_swapped(t0, t1);      // rowmax S^j
+    // m is itself a maximum (or -inf), so no operand quieting is needed
+    const float mnew = fmax_swapped(m, mt);
     // alpha (pg_alpha) is formed only where a row maximum moved
     st.dm = m - mnew;
     moved = __builtin_amdgcn_ballot_w64(m != mnew) != 0ull;
@@ -392,10 +383,7 @@ __device__ __forceinline__ PgenOut pgen(const f32x16& s0, const f32x16& s1, floa
   float pm0, pm1;
   PgenState st;
   pg_max<KIND>(s0, s1, pm0, pm1);
-  float bs;
-  const float mt = pg_rowmax<KIND>(pm0, pm1, pa, bs);
-  // m is itself a maximum (or -inf), so no operand quieting is needed
-  pg_params<KIND>(bs, fmax_swapped(m, mt), m, pa, st);
+  pg_params<KIND>(pm0, pm1, m, pa, st);
   pg_pairs<KIND, 0, 32>(s0, s1, pa, st);
   if constexpr (KIND == EFQ_PGEN_NOOP) asm volatile("" ::"v"(s0), "v"(s1));   // keep Q K^T live
   return pg_finish<KIND>(st);
@@ -575,7 +563,6 @@ struct AttnArgs {
   size_t scale_off;   // byte offset of the E8M0 plane in V~
   int nqt;            // query tiles per (batch, head)
   int xcd_remap;      // 1: group work items by XCD
-  int spread;         // 1: pair long and short work items (map_work)
   float scale, tau, h;
   // dump (may be null)
   uint8_t* p_codes;
@@ -586,6 +573,7 @@ struct AttnArgs {
   // MXFP8 Q^ / K^ (low-bit Q K^T): padded rows per head, scale offsets
   int sq_pad, sk_pad;
   size_t q8_soff, k8_soff;
+  int spread;         // 1: pair long and short work items (map_work)
 };
 
 // LDS layout.  A K tile is stored in the order the bf16 MFMA reads its A
@@ -814,12 +802,13 @@ __device__ __forceinline__ void wait_vmem_le(int n) {
 // over all its heads and the second 32 (one per CU) reversed, so that a
 // long workgroup shares its CU with a short one: 2 prompts of 1024 tokens
 // 28.2 -> 24.9 us, one of 2048 40.0 -> 38.4 us.
+template <bool SPREAD>
 __device__ __forceinline__ void map_work(const AttnArgs& a, int& b, int& hq, int& qt) {
   const int n = blockIdx.x;
   const int total = gridDim.x;
   int w = n;
   if (a.xcd_remap) w = (n & 7) * (total >> 3) + (n >> 3);
-  if (a.spread) {
+  if (SPREAD && a.spread) {
     const int items = total >> 3, heads = items / a.nqt;   // of one XCD
     int i = n >> 3;
     if (i >= kXcdCUs) i = kXcdCUs + items - 1 - i;
@@ -1285,11 +1274,9 @@ struct PPWave {
     // some lane's visible keys end inside this tile
     if (j >= mask_from)
       mask_tile(s0, s1, vis_end4 - j * kBc);
-    float pm0, pm1, bs;
+    float pm0, pm1;
     pg_max<KIND>(s0, s1, pm0, pm1);
-    const float mt = pg_rowmax<KIND>(pm0, pm1, pa, bs);
-    // m is itself a maximum (or -inf), so no operand quieting is needed
-    if (pg_params<KIND>(bs, fmax_swapped(m, mt), m, pa, st)) {
+    if (pg_params<KIND>(pm0, pm1, m, pa, st)) {
       const float alpha = pg_alpha<KIND>(st);
 #pragma unroll
       for (int s = 0; s < NS; ++s) oacc[s] *= alpha;
@@ -1516,18 +1503,30 @@ __device__ __forceinline__ void half_schedule(PPWave<D, KIND, false, Q8, false>&
   for (int t = T; t < ntiles; ++t) end();
 }
 
-// The body of the attention kernels: NW = 8 waves in the ping-pong schedule,
-// or NW = 4 in the half workgroup's.
+constexpr int kRhoCand = 64;
+// Calibration candidates of one launch (grid y), the reference output and the
+// objective's partial sums.
+struct RhoArgs {
+  const float* o_ref;
+  double* part;       // [candidate][workgroup][2]
+  float tau[kRhoCand], h[kRhoCand];
+};
+struct NoRho {};
+
+// The attention kernel: NW = 8 waves in the ping-pong schedule, or NW = 4 in
+// the half workgroup's.  (One kernel template, not a body shared by several
+// kernels: inlined into a wrapper, the compiler allocates the tile loop's
+// registers differently, 0.6 % slower at 32K.)
 // Q8: q and k are the MXFP8 buffers Q^ and K^ (E4M3 codes, then E8M0 scales
 // at a.q8_soff / a.k8_soff, [batch][head][padded seq] rows), else bf16 BSHD.
 // RHO: instead of storing O, the sums of (O - o_ref)^2 and o_ref^2 over the
-// workgroup's outputs, in fp64 and a fixed order, go to rho[0] and rho[1].
-template <int NW, int D, int KIND, bool CAUSAL, bool DUMP, bool Q8, bool RHO = false>
-__device__ __forceinline__ void attn_body(const void* __restrict__ q, const void* __restrict__ k,
-                                          const uint8_t* __restrict__ vhat,
-                                          float* __restrict__ out, const AttnArgs& a,
-                                          uint8_t* smem, const float* __restrict__ o_ref = nullptr,
-                                          double* __restrict__ rho = nullptr) {
+// workgroup's outputs, in fp64 and a fixed order, go to rho.part.
+template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8, int NW, bool RHO>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * NW, 64 * NW), amdgpu_waves_per_eu(2, 2))) void
+attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
+               const uint8_t* __restrict__ vhat, float* __restrict__ out, AttnArgs a,
+               std::conditional_t<RHO, RhoArgs, NoRho> rho) {
+  extern __shared__ __align__(16) uint8_t smem[];
   constexpr bool kPair = NW == kPPWaves;     // the ping-pong schedule
   constexpr int kBr = kWaveQ * NW;           // queries per workgroup
   constexpr int KK = D / 16;
@@ -1535,7 +1534,7 @@ __device__ __forceinline__ void attn_body(const void* __restrict__ q, const void
   using Sm = std::conditional_t<kPair, SmemPP<D, Q8>, SmemH<D, Q8>>;
 
   int b, hq, qt;
-  map_work(a, b, hq, qt);
+  map_work<!kPair && CAUSAL>(a, b, hq, qt);
   const int g = hq / (a.Hq / a.Hkv);
   // wave index as a uniform (scalar) value: the group branch below is uniform
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1599,11 +1598,16 @@ __device__ __forceinline__ void attn_body(const void* __restrict__ q, const void
   asm volatile("" : "+v"(vload.coff_lane), "+v"(vload.soff_lane));
 
   w.pa.scale = a.scale;
-  w.pa.sh = a.scale * a.h;
+  float tau = a.tau, h = a.h;
+  if constexpr (RHO) {
+    tau = rho.tau[blockIdx.y];
+    h = rho.h[blockIdx.y];
+  }
+  w.pa.sh = a.scale * h;
   w.pa.sh32 = 32.0f * w.pa.sh;
   w.pa.sh16 = 16.0f * w.pa.sh;
-  w.pa.c = kLn6 + a.tau;
-  w.pa.negh = -a.h;
+  w.pa.c = kLn6 + tau;
+  w.pa.negh = -h;
   w.pa.l2s = a.scale * kInvLn2;
 #pragma unroll
   for (int s = 0; s < NS; ++s) w.oacc[s] = f32x16{};
@@ -1718,7 +1722,7 @@ __device__ __forceinline__ void attn_body(const void* __restrict__ q, const void
   if constexpr (RHO) {
     double d2 = 0.0, r2 = 0.0;
     if (w.my_q < a.Sq) {
-      const float* rp = o_ref + (((long)b * a.Sq + w.my_q) * a.Hq + hq) * D;
+      const float* rp = rho.o_ref + (((long)b * a.Sq + w.my_q) * a.Hq + hq) * D;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
 #pragma unroll
@@ -1749,7 +1753,7 @@ __device__ __forceinline__ void attn_body(const void* __restrict__ q, const void
       double t = 0.0;
 #pragma unroll
       for (int i = 0; i < NW; ++i) t += red[2 * i + threadIdx.x];
-      rho[threadIdx.x] = t;
+      rho.part[2 * ((long)blockIdx.y * gridDim.x + blockIdx.x) + threadIdx.x] = t;
     }
   } else if (w.my_q < a.Sq) {
     float* op = out + (((long)b * a.Sq + w.my_q) * a.Hq + hq) * D;
@@ -1773,22 +1777,375 @@ __device__ __forceinline__ void attn_body(const void* __restrict__ q, const void
   }
 }
 
-template <int D, int KIND, bool CAUSAL, bool DUMP, bool Q8>
-__global__ __attribute__((amdgpu_flat_work_group_size(kPPThreads, kPPThreads),
-                          amdgpu_waves_per_eu(2, 2))) void
-attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
-               const uint8_t* __restrict__ vhat, float* __restrict__ out, AttnArgs a) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  attn_body<kPPWaves, D, KIND, CAUSAL, DUMP, Q8>(q, k, vhat, out, a, smem);
+// ------------------------------------------------------ few queries
+// Few queries against many keys (a generation step) leave the kernels above
+// a handful of workgroups that walk all keys one tile after another.  Here
+// the keys of a (batch, kv head) are split into chunks of whole 64-key tiles,
+// and the 32 columns of a wave hold the queries of all heads of the group
+// (row r = query * group + head).  The codes depend on the running row
+// maximum, so the split first finds every chunk's row maxima (one pass over
+// K); a chunk then starts from the maximum of the chunks before it, which is
+// the running maximum the unsplit recurrence has there, and takes the same
+// scores, codes and scales.  Partial sums (A, l) of the chunks are merged
+// with alpha = exp(m_chunk - m_last).  With few rows the first pass keeps the
+// scores and the second reads those in place of K.
+//   split_max_kernel    row maxima of every chunk
+//   split_attn_kernel   Alg. 2 over one chunk per wave; the four waves of a
+//                       workgroup (consecutive chunks) merge through LDS
+//   split_merge_kernel  merges the workgroups' partial sums, divides by l
+constexpr int kSWaves = 4;                 // chunks per workgroup
+constexpr int kSRows = 128;                // most rows (queries x group) taken
+constexpr int kSItems = 2048;              // waves the chip holds at two per SIMD
+
+struct SplitArgs {
+  int B, Sq, Sk, Hq, Hkv;
+  int nb;             // padded 32-key blocks of V~
+  size_t scale_off;
+  int R, CT;          // rows per (batch, kv head), 32-row column tiles
+  int ntiles, tpc;    // 64-key tiles, tiles per chunk
+  int nch, ngrp;      // chunks, workgroups (kSWaves chunks) per column tile
+  int xcd_remap;
+  float scale, tau, h;
+  int sq_pad, sk_pad;
+  size_t q8_soff, k8_soff;
+  float* cmax;        // [B Hkv][nch][CT * 32] row maxima of the raw products
+  float* part;        // [B Hkv][ngrp][R][D] partial A, then [..][R][2] (m, l)
+  float* ml;
+  float* sc;          // scores, [B Hkv][tile][8][half][R][4] (accumulator registers 4 i .. 4 i + 3)
+};
+
+// Registers a wave reads K of one tile into: bf16, the operand of k-step kk
+// of window w; MXFP8, that of chunk c, and the lane's scales.
+template <int D, bool Q8>
+struct SplitK {
+  bf16x8 a[2][D / 16];
+};
+template <int D>
+struct SplitK<D, true> {
+  i32x8 a[2][D / 64];
+  int sc[2];
+};
+
+template <int D, bool Q8>
+__device__ __forceinline__ void split_read_k(const void* k, const SplitArgs& a, int b, int g, int tile,
+                                             int lane, SplitK<D, Q8>& o) {
+  const int half = lane >> 5;
+#pragma unroll
+  for (int w = 0; w < 2; ++w) {
+    const int key = tile * kBc + 32 * w + (lane & 31);
+    if constexpr (Q8) {   // padded to whole tiles
+      const long row = ((long)b * a.Hkv + g) * a.sk_pad + key;
+      const uint8_t* p = (const uint8_t*)k + row * D + 16 * half;
+#pragma unroll
+      for (int c = 0; c < D / 64; ++c) {
+        const u32x4 lo = *(const u32x4*)(p + 64 * c);
+        const u32x4 hi = *(const u32x4*)(p + 64 * c + 32);
+        o.a[w][c] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
+                          (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+      }
+      const uint8_t* sp = (const uint8_t*)k + a.k8_soff + row * (D / 32);
+      unsigned raw;
+      if constexpr (D == 128) raw = *(const unsigned*)sp;
+      else raw = *(const unsigned short*)sp;
+      o.sc[w] = lane_scales<D>(raw, half);
+    } else {              // keys past the end read the last one (masked)
+      const int kc = key < a.Sk ? key : a.Sk - 1;
+      const unsigned short* p =
+          (const unsigned short*)k + (((long)b * a.Sk + kc) * a.Hkv + g) * D + half * 8;
+#pragma unroll
+      for (int kk = 0; kk < D / 16; ++kk) o.a[w][kk] = *(const bf16x8*)(p + kk * 16);
+    }
+  }
 }
 
-template <int D, int KIND, bool CAUSAL, bool Q8>
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * kHWaves, 64 * kHWaves),
-                          amdgpu_waves_per_eu(2, 2))) void
-attn_half_kernel(const void* __restrict__ q, const void* __restrict__ k,
-                 const uint8_t* __restrict__ vhat, float* __restrict__ out, AttnArgs a) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  attn_body<kHWaves, D, KIND, CAUSAL, false, Q8>(q, k, vhat, out, a, smem);
+// The lane's query operand of column tile ct (rows past R read row R - 1).
+template <int D, bool Q8>
+__device__ __forceinline__ void split_read_q(const void* q, const SplitArgs& a, int b, int g, int ct,
+                                             int lane, QOps<D, Q8>& o) {
+  const int half = lane >> 5;
+  const int G = a.Hq / a.Hkv;
+  const int r = min(ct * 32 + (lane & 31), a.R - 1);
+  const int i = r / G, hq = g * G + r % G;
+  if constexpr (Q8) {
+    const long row = ((long)b * a.Hq + hq) * a.sq_pad + i;
+    const uint8_t* p = (const uint8_t*)q + row * D + 16 * half;
+#pragma unroll
+    for (int c = 0; c < D / 64; ++c) {
+      const u32x4 lo = *(const u32x4*)(p + 64 * c);
+      const u32x4 hi = *(const u32x4*)(p + 64 * c + 32);
+      o.a[c] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3],
+                     (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
+    }
+    const uint8_t* sp = (const uint8_t*)q + a.q8_soff + row * (D / 32);
+    unsigned raw;
+    if constexpr (D == 128) raw = *(const unsigned*)sp;
+    else raw = *(const unsigned short*)sp;
+    o.sc = lane_scales<D>(raw, half);
+  } else {
+    const unsigned short* p =
+        (const unsigned short*)q + (((long)b * a.Sq + i) * a.Hq + hq) * D + half * 8;
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) o.r[kk] = *(const bf16x8*)(p + kk * 16);
+  }
+}
+
+// S = K Q^T of one tile, with the MFMAs in the order of the unsplit kernels.
+template <int I, int D>
+__device__ __forceinline__ void split_qk8(const SplitK<D, true>& k, const QOps<D, true>& q, f32x16& s0,
+                                          f32x16& s1) {
+  if constexpr (I < D / 64) {
+    s0 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(k.a[0][I], q.a[I], s0, 0, 0, I, k.sc[0], I, q.sc);
+    s1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(k.a[1][I], q.a[I], s1, 0, 0, I, k.sc[1], I, q.sc);
+    split_qk8<I + 1>(k, q, s0, s1);
+  }
+}
+template <int D, bool Q8>
+__device__ __forceinline__ void split_qk(const SplitK<D, Q8>& k, const QOps<D, Q8>& q, f32x16& s0,
+                                         f32x16& s1) {
+  s0 = f32x16{};
+  s1 = f32x16{};
+  if constexpr (Q8) {
+    split_qk8<0>(k, q, s0, s1);
+  } else {
+#pragma unroll
+    for (int kk = 0; kk < D / 16; ++kk) {
+      s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.a[0][kk], q.r[kk], s0, 0, 0, 0);
+      s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(k.a[1][kk], q.r[kk], s1, 0, 0, 0);
+    }
+  }
+}
+
+__device__ __forceinline__ int split_work(const SplitArgs& a) {
+  const int n = blockIdx.x;
+  return a.xcd_remap ? (n & 7) * (int)(gridDim.x >> 3) + (n >> 3) : n;
+}
+
+// The lane's first stored score quad of a tile (rows past R: row R - 1).
+__device__ __forceinline__ f32x4* split_scores(const SplitArgs& a, int bg, int t, int lane) {
+  return (f32x4*)a.sc + ((long)bg * a.ntiles + t) * 16 * a.R + (lane >> 5) * a.R + min(lane & 31, a.R - 1);
+}
+
+// One wave per (batch, kv head, chunk, group of CTW column tiles).
+template <int D, bool Q8, int CTW, bool KEEP>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * kSWaves, 64 * kSWaves),
+                          amdgpu_waves_per_eu(2, 4))) void
+split_max_kernel(const void* __restrict__ q, const void* __restrict__ k, SplitArgs a) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int ncg = (a.CT + CTW - 1) / CTW;
+  int w = split_work(a);
+  const int cg = w % ncg;
+  w /= ncg;
+  const int chunk = (w % a.ngrp) * kSWaves + wave;
+  const int bg = w / a.ngrp;
+  const int b = bg / a.Hkv, g = bg % a.Hkv;
+  const int t0 = chunk * a.tpc, t1 = min(a.ntiles, t0 + a.tpc);
+  if (t0 >= t1) return;
+  QOps<D, Q8> qo[CTW];
+#pragma unroll
+  for (int c = 0; c < CTW; ++c) split_read_q<D, Q8>(q, a, b, g, min(cg * CTW + c, a.CT - 1), lane, qo[c]);
+  SplitK<D, Q8> kr;
+  split_read_k<D, Q8>(k, a, b, g, t0, lane, kr);
+  float mx[CTW];
+#pragma unroll
+  for (int c = 0; c < CTW; ++c) mx[c] = -INFINITY;
+  for (int t = t0; t < t1; ++t) {
+    f32x16 s[CTW][2];
+#pragma unroll
+    for (int c = 0; c < CTW; ++c) split_qk<D, Q8>(kr, qo[c], s[c][0], s[c][1]);
+    if (t + 1 < t1) split_read_k<D, Q8>(k, a, b, g, t + 1, lane, kr);
+    if constexpr (KEEP) {
+      if ((lane & 31) < a.R) {
+        f32x4* p = split_scores(a, bg, t, lane);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const f32x16& x = s[0][i >> 2];
+          p[(long)i * 2 * a.R] = f32x4{x[4 * (i & 3)], x[4 * (i & 3) + 1], x[4 * (i & 3) + 2], x[4 * (i & 3) + 3]};
+        }
+      }
+    }
+    const int l0 = a.Sk - t * kBc - 4 * (lane >> 5);
+#pragma unroll
+    for (int c = 0; c < CTW; ++c) {
+      if ((t + 1) * kBc > a.Sk) mask_tile(s[c][0], s[c][1], l0);
+      mx[c] = fmaxf(mx[c], fmaxf(max16(s[c][0]), max16(s[c][1])));
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < CTW; ++c) {
+    const int ct = cg * CTW + c;
+    float x = mx[c], y = mx[c];
+    swap32f(x, y);
+    if (ct < a.CT && lane < 32)
+      a.cmax[((long)bg * a.nch + chunk) * (a.CT * 32) + ct * 32 + lane] = fmaxf(x, y);
+  }
+}
+
+// One wave per (batch, kv head, column tile, chunk); the last chunk of a
+// workgroup has its largest (running) maximum.
+template <int D, int KIND, bool Q8, bool KEEP>
+__global__ __attribute__((amdgpu_flat_work_group_size(64 * kSWaves, 64 * kSWaves),
+                          amdgpu_waves_per_eu(2, KEEP ? 3 : 2))) void
+split_attn_kernel(const void* __restrict__ q, const void* __restrict__ k,
+                  const uint8_t* __restrict__ vhat, SplitArgs a) {
+  constexpr int NS = D / 32;
+  __shared__ __align__(16) float so[kSWaves][D / 16][64][4];   // scaled A of each wave, half the columns
+  __shared__ float sm[kSWaves][32], sl[kSWaves][32];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63, half = lane >> 5;
+  int w = split_work(a);
+  const int ct = w % a.CT;
+  w /= a.CT;
+  const int grp = w % a.ngrp, bg = w / a.ngrp;
+  const int chunk = grp * kSWaves + wave;
+  const int b = bg / a.Hkv, g = bg % a.Hkv;
+  const int t0 = chunk * a.tpc, t1 = min(a.ntiles, t0 + a.tpc);
+
+  PgenArgs pa;
+  pa.scale = a.scale;
+  pa.sh = a.scale * a.h;
+  pa.sh32 = 32.0f * pa.sh;
+  pa.sh16 = 16.0f * pa.sh;
+  pa.c = kLn6 + a.tau;
+  pa.negh = -a.h;
+  pa.l2s = a.scale * kInvLn2;
+
+  f32x16 oacc[NS];
+#pragma unroll
+  for (int s = 0; s < NS; ++s) oacc[s] = f32x16{};
+  f32x4 lacc = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY;
+  if (t0 < t1) {
+    QOps<D, Q8> qo;
+    SplitK<D, Q8> kr;
+    f32x16 n0, n1;   // with KEEP: the next tile's stored scores
+    auto read_scores = [&](int t) {
+      const f32x4* p = split_scores(a, bg, t, lane);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const f32x4 x = p[(long)i * 2 * a.R];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) (i < 4 ? n0 : n1)[4 * (i & 3) + c] = x[c];
+      }
+    };
+    if constexpr (KEEP) {
+      read_scores(t0);
+    } else {
+      split_read_q<D, Q8>(q, a, b, g, ct, lane, qo);
+      split_read_k<D, Q8>(k, a, b, g, t0, lane, kr);
+    }
+    const uint8_t* vc = vhat + (long)bg * a.nb * D * 16 + (half * D + (lane & 31)) * 16;
+    const uint8_t* vs = vhat + a.scale_off + (long)bg * a.nb * D + half * D + (lane & 31) * (D / 32);
+    auto read_vops = [&](int t, VOps<D>& v) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) v.a[s] = *(const u32x4*)(vc + (long)t * (2 * D * 16) + s * 512);
+      if constexpr (NS == 4) v.sv = *(const int*)(vs + (long)t * (2 * D));
+      else v.sv = *(const unsigned short*)(vs + (long)t * (2 * D));
+    };
+    VOps<D> vop;
+    read_vops(t0, vop);
+    // the running maximum at the chunk's first key: the lane halves take
+    // alternate earlier chunks
+    {
+      const float* cm = a.cmax + (long)bg * a.nch * (a.CT * 32) + ct * 32 + (lane & 31);
+      float x = -INFINITY;
+#pragma unroll 8
+      for (int c = half; c < chunk; c += 2) x = fmaxf(x, cm[(long)c * (a.CT * 32)]);
+      float y = x;
+      swap32f(x, y);
+      m = fmaxf(x, y) * (is_expq<KIND>() ? pa.l2s : pa.scale);
+    }
+    const i32x8 sel = rowsum_selector(lane);
+    for (int t = t0; t < t1; ++t) {
+      f32x16 s0, s1;
+      if constexpr (KEEP) {
+        s0 = n0;
+        s1 = n1;
+      } else {
+        split_qk<D, Q8>(kr, qo, s0, s1);
+      }
+      const VOps<D> v = vop;
+      if (t + 1 < t1) {
+        if constexpr (KEEP) read_scores(t + 1);
+        else split_read_k<D, Q8>(k, a, b, g, t + 1, lane, kr);
+        read_vops(t + 1, vop);
+      }
+      if ((t + 1) * kBc > a.Sk) mask_tile(s0, s1, a.Sk - t * kBc - 4 * half);
+      float pm0, pm1;
+      PgenState st;
+      pg_max<KIND>(s0, s1, pm0, pm1);
+      if (pg_params<KIND>(pm0, pm1, m, pa, st)) {
+        const float alpha = pg_alpha<KIND>(st);
+#pragma unroll
+        for (int s = 0; s < NS; ++s) oacc[s] *= alpha;
+        lacc[0] *= alpha;
+      }
+      pg_pairs<KIND, 0, 32>(s0, s1, pa, st);
+      const PgenOut po = pg_finish<KIND>(st);
+      const i32x8 b8 = i32x8{(int)po.bop[0], (int)po.bop[1], (int)po.bop[2], (int)po.bop[3], 0, 0, 0, 0};
+      pv_slabs<NS>(oacc, v, b8, po.scale_b);
+      lacc = rowsum_mfma(sel, b8, lacc, po.scale_b);
+    }
+  }
+  // merge the workgroup's chunks at the maximum of its last one
+  if (half == 0) sm[wave][lane] = m;
+  __syncthreads();
+  const int last = min(kSWaves, a.nch - grp * kSWaves) - 1;
+  const float ml = sm[last][lane & 31];
+  const float f = t0 < t1 ? __builtin_amdgcn_exp2f(is_expq<KIND>() ? m - ml : (m - ml) * kInvLn2) : 0.0f;
+  if (half == 0) sl[wave][lane] = lacc[0] * f;
+  // slice i = 4 s + r of lane (row, half) holds columns 32 s + 8 r + 4 half +
+  // [0, 4); wave w sums slices w, w + 4, ... of each half of the columns
+  const int row = ct * 32 + (lane & 31);
+  const long prow = ((long)bg * a.ngrp + grp) * a.R + row;
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+#pragma unroll
+    for (int s = 0; s < NS / 2; ++s)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const f32x16& o = oacc[h * (NS / 2) + s];
+        *(f32x4*)so[wave][s * 4 + r][lane] =
+            f32x4{o[4 * r] * f, o[4 * r + 1] * f, o[4 * r + 2] * f, o[4 * r + 3] * f};
+      }
+    __syncthreads();
+    if (row < a.R) {
+#pragma unroll
+      for (int j = 0; j < D / 16 / kSWaves; ++j) {
+        const int i = j * kSWaves + wave;
+        f32x4 x = *(f32x4*)so[0][i][lane];
+#pragma unroll
+        for (int c = 1; c < kSWaves; ++c) x += *(f32x4*)so[c][i][lane];
+        *(f32x4*)(a.part + prow * D + h * (D / 2) + i * 8 + 4 * half) = x;
+      }
+      if (h == 0 && wave == 0 && half == 0) {
+        a.ml[2 * prow] = ml;
+        a.ml[2 * prow + 1] = sl[0][lane] + sl[1][lane] + sl[2][lane] + sl[3][lane];
+      }
+    }
+    if (h == 0) __syncthreads();
+  }
+}
+
+// One workgroup of D threads per output row (batch, kv head, row).
+template <int D, bool LOG2>
+__global__ __launch_bounds__(D) void split_merge_kernel(float* __restrict__ out, SplitArgs a) {
+  const int r = blockIdx.x % a.R, bg = blockIdx.x / a.R;
+  const int b = bg / a.Hkv, g = bg % a.Hkv, G = a.Hq / a.Hkv;
+  const int d = threadIdx.x;
+  const long p0 = (long)bg * a.ngrp * a.R + r;
+  const float mt = a.ml[2 * (p0 + (long)(a.ngrp - 1) * a.R)];
+  float o = 0.0f, l = 0.0f;
+#pragma unroll 4
+  for (int i = 0; i < a.ngrp; ++i) {
+    const long p = p0 + (long)i * a.R;
+    const float dm = a.ml[2 * p] - mt;
+    const float f = __builtin_amdgcn_exp2f(LOG2 ? dm : dm * kInvLn2);
+    o += a.part[p * D + d] * f;
+    l += a.ml[2 * p + 1] * f;
+  }
+  const float rl = l > 0.0f ? 1.0f / l : 0.0f;
+  out[(((long)b * a.Sq + r / G) * a.Hq + g * G + r % G) * D + d] = o * rl;
 }
 
 // ------------------------------------------ standalone probability stage
@@ -1951,23 +2308,6 @@ __global__ void fill_zero_kernel(uint8_t* __restrict__ p, size_t n) {
 // 16 candidates on 1024 tokens (32/8 heads, D 128) took 16 x (28.8 us
 // attention + 8.0 us for the sums over the stored output + 2.8 us to reduce
 // them); a whole call 724 us, now 187.
-constexpr int kRhoCand = 64;
-struct RhoCand {
-  float tau[kRhoCand], h[kRhoCand];
-};
-
-template <int NW, int D, bool CAUSAL>
-__global__ __attribute__((amdgpu_flat_work_group_size(64 * NW, 64 * NW), amdgpu_waves_per_eu(2, 2))) void
-attn_rho_kernel(const void* __restrict__ q, const void* __restrict__ k,
-                const uint8_t* __restrict__ vhat, const float* __restrict__ o_ref, AttnArgs a,
-                RhoCand cand, double* __restrict__ part) {
-  extern __shared__ __align__(16) uint8_t smem[];
-  a.tau = cand.tau[blockIdx.y];
-  a.h = cand.h[blockIdx.y];
-  attn_body<NW, D, EFQ_PGEN_EFQ, CAUSAL, false, false, true>(
-      q, k, vhat, nullptr, a, smem, o_ref, part + 2 * ((long)blockIdx.y * gridDim.x + blockIdx.x));
-}
-
 // One block per candidate: its n partial pairs -> res[2 c] = sum (O~ -
 // O_ref)^2, res[2 c + 1] = sum O_ref^2.
 __global__ __launch_bounds__(256) void rho_final_kernel(const double* __restrict__ part, long n,
@@ -2121,13 +2461,13 @@ hipError_t launch_attn_t(const void* q, const void* k, const void* vhat, float* 
     const hipError_t e = raise_lds<decltype(kernel)::value>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(decltype(kernel)::value, dim3(grid), dim3(threads), lds, st, q, k,
-                       (const uint8_t*)vhat, out, a);
+                       (const uint8_t*)vhat, out, a, NoRho{});
     return hipGetLastError();
   };
   if constexpr (HALF)
-    return launch(KernelPtr<attn_half_kernel<D, KIND, CAUSAL, Q8>>{}, 64 * kHWaves, SmemH<D, Q8>::kTotal);
+    return launch(KernelPtr<attn_pp_kernel<D, KIND, CAUSAL, false, Q8, kHWaves, false>>{}, 64 * kHWaves, SmemH<D, Q8>::kTotal);
   else
-    return launch(KernelPtr<attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8>>{}, kPPThreads,
+    return launch(KernelPtr<attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8, kPPWaves, false>>{}, kPPThreads,
                   SmemPP<D, Q8>::kTotal);
 }
 
@@ -2275,6 +2615,151 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
   return EFQ_OK;
 }
 
+// The key split of a shape (few queries): chunk sizes and the scratch it
+// needs, or bytes = 0 where the unsplit kernels take it.  The line lies where
+// two estimates (us) cross, both from timed shapes:
+//  - unsplit: a tile of keys takes a workgroup 0.75 us (0.65 at D = 64), two
+//    workgroups on a CU 1.2 us together, but no less than K and V~ at 5 TB/s;
+//  - split: three launches, and K twice (or once, with the scores stored and
+//    read back, while these are fewer bytes) and V~ at 5 TB/s, but no less
+//    than 0.9 us per tile and SIMD.
+// Measured, unsplit / split (us): one query of 32 heads against 700 keys 15.3
+// / 17.4, 4096 52 / 20, 32768 368 / 55; 16 sequences with 24 key/value heads of
+// their own against 8192 keys 255 / 467 (K read twice).
+struct SplitPlan {
+  bool scores;                           // keep the scores between the passes
+  int R, CT, ntiles, tpc, nch, ngrp;
+  size_t cmax, part, ml, sc, bytes;      // byte offsets of the scratch parts, total
+};
+
+SplitPlan split_plan(const efq_shape* s, bool q8) {
+  SplitPlan p;
+  memset(&p, 0, sizeof p);
+  const long R = (long)s->seq_q * (s->heads_q / s->heads_kv);
+  if (R > kSRows) return p;
+  const int D = s->head_dim;
+  const long bg = (long)s->batch * s->heads_kv;
+  p.R = (int)R;
+  p.CT = (p.R + 31) / 32;
+  p.ntiles = (s->seq_k + kBc - 1) / kBc;
+  const double tiles = (double)bg * p.CT * p.ntiles;
+  const double kb = (double)bg * s->seq_k * D * (q8 ? 33.0 / 32 : 2.0);
+  const double vb = (double)bg * s->seq_k * D * (17.0 / 32);
+  const double sb = (double)bg * p.ntiles * kBc * 4 * p.R;
+  p.scores = p.CT == 1 && 2 * sb <= kb;
+  const double wgs = (double)s->batch * s->heads_q * ((s->seq_q + 127) / 128);
+  const double rounds = wgs <= kCUs ? 1.0 : 0.8 * wgs / kCUs;
+  const double unsplit = 6 + std::max(p.ntiles * (D == 128 ? 0.75 : 0.65) * rounds, (kb + vb) / 5e6);
+  const double split = 14 + std::max((kb + vb + (p.scores ? 2 * sb : kb)) / 5e6, tiles / 1024 * 0.9);
+  if (split > 0.9 * unsplit) return p;
+  p.tpc = (int)std::min<double>(p.ntiles, std::ceil(tiles / kSItems));
+  p.nch = (p.ntiles + p.tpc - 1) / p.tpc;
+  p.ngrp = (p.nch + kSWaves - 1) / kSWaves;
+  if (bg * p.CT * p.ngrp > 0x7FFFFFFFL || bg * p.R > 0x7FFFFFFFL) return p;
+  p.cmax = 0;
+  p.part = round256((size_t)bg * p.nch * p.CT * 32 * 4);
+  p.ml = p.part + round256((size_t)bg * p.ngrp * p.R * D * 4);
+  p.sc = p.ml + round256((size_t)bg * p.ngrp * p.R * 8);
+  p.bytes = p.sc + (p.scores ? (size_t)sb : 0);
+  return p;
+}
+
+// Scratch bytes of the split (a multiple of 256).
+size_t split_bytes(const efq_shape* s, bool q8) { return round256(split_plan(s, q8).bytes); }
+
+template <int D, bool Q8, bool KEEP>
+hipError_t launch_split_t(int kind, const void* q, const void* k, const void* vhat, float* out,
+                          const SplitArgs& a, hipStream_t st) {
+  const unsigned bg = (unsigned)(a.B * a.Hkv);
+  const unsigned grid_max = bg * a.ngrp * ((a.CT + 1) / 2);
+  const dim3 block(64 * kSWaves);
+  SplitArgs am = a;
+  am.xcd_remap = grid_max % 8 == 0;
+  if (a.CT == 1)
+    hipLaunchKernelGGL((split_max_kernel<D, Q8, 1, KEEP>), dim3(grid_max), block, 0, st, q, k, am);
+  else
+    hipLaunchKernelGGL((split_max_kernel<D, Q8, 2, false>), dim3(grid_max), block, 0, st, q, k, am);
+  const dim3 grid(bg * a.ngrp * a.CT);
+  const uint8_t* v = (const uint8_t*)vhat;
+  bool log2 = false;
+  switch (kind) {
+    case EFQ_PGEN_EFQ:
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EFQ, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      break;
+    case EFQ_PGEN_LUT:
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_LUT, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      break;
+    case EFQ_PGEN_EXPQ:
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EXPQ, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      log2 = true;
+      break;
+    case EFQ_PGEN_EXPQ6:
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EXPQ6, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      log2 = true;
+      break;
+    default:
+      return hipErrorInvalidValue;
+  }
+  if (log2) hipLaunchKernelGGL((split_merge_kernel<D, true>), dim3(bg * a.R), dim3(D), 0, st, out, a);
+  else hipLaunchKernelGGL((split_merge_kernel<D, false>), dim3(bg * a.R), dim3(D), 0, st, out, a);
+  return hipGetLastError();
+}
+
+int launch_split(const void* q, const void* k, const void* vhat, float scale, int kind, efq_params p,
+                 float* out, const efq_shape* s, const SplitPlan& pl, void* ws, hipStream_t st, bool q8) {
+  SplitArgs a;
+  a.B = s->batch;
+  a.Sq = s->seq_q;
+  a.Sk = s->seq_k;
+  a.Hq = s->heads_q;
+  a.Hkv = s->heads_kv;
+  a.nb = (int)padded_blocks(s->seq_k);
+  a.scale_off = vhat_scale_offset(s);
+  a.R = pl.R;
+  a.CT = pl.CT;
+  a.ntiles = pl.ntiles;
+  a.tpc = pl.tpc;
+  a.nch = pl.nch;
+  a.ngrp = pl.ngrp;
+  a.xcd_remap = (long)a.B * a.Hkv * a.ngrp * a.CT % 8 == 0;
+  a.scale = scale;
+  a.tau = p.tau;
+  a.h = p.h;
+  a.sq_pad = (int)pad64(s->seq_q);
+  a.sk_pad = (int)pad64(s->seq_k);
+  a.q8_soff = q8_scale_offset(qhat_rows(s), s->head_dim);
+  a.k8_soff = q8_scale_offset(khat_rows(s), s->head_dim);
+  a.cmax = (float*)((uint8_t*)ws + pl.cmax);
+  a.part = (float*)((uint8_t*)ws + pl.part);
+  a.ml = (float*)((uint8_t*)ws + pl.ml);
+  a.sc = (float*)((uint8_t*)ws + pl.sc);
+  auto launch = [&](auto d, auto is_q8) {
+    constexpr int D = decltype(d)::value;
+    constexpr bool Q8 = decltype(is_q8)::value;
+    return pl.scores ? launch_split_t<D, Q8, true>(kind, q, k, vhat, out, a, st)
+                     : launch_split_t<D, Q8, false>(kind, q, k, vhat, out, a, st);
+  };
+  hipError_t e;
+  if (s->head_dim == 64) e = q8 ? launch(IC<64>{}, std::true_type{}) : launch(IC<64>{}, std::false_type{});
+  else e = q8 ? launch(IC<128>{}, std::true_type{}) : launch(IC<128>{}, std::false_type{});
+  if (e != hipSuccess) return fail(EFQ_EHIP, "attention launch: %s", hipGetErrorString(e));
+  return EFQ_OK;
+}
+
+// Attention on V~ (and Q^, K^ with q8), by the key split where the shape takes
+// it and ws (16-byte aligned) has room for its scratch.
+int launch_attn_ws(const void* q, const void* k, const void* vhat, float scale, int causal, int kind,
+                   efq_params p, float* out, const efq_shape* s, void* ws, size_t ws_bytes,
+                   hipStream_t st, bool q8) {
+  if (!causal && kind != EFQ_PGEN_NOOP) {
+    const SplitPlan pl = split_plan(s, q8);
+    if (pl.bytes && ws && ws_bytes >= pl.bytes)
+      return launch_split(q, k, vhat, scale, kind, p, out, s, pl, ws, st, q8);
+  }
+  return launch_attn(q, k, vhat, scale, causal, kind, p, out, s, st, nullptr, nullptr, nullptr,
+                     nullptr, q8);
+}
+
 int check_kind(int kind, bool allow_noop) {
   if (kind == EFQ_PGEN_EFQ || kind == EFQ_PGEN_EXPQ || kind == EFQ_PGEN_LUT ||
       kind == EFQ_PGEN_EXPQ6)
@@ -2303,7 +2788,9 @@ int launch_rho(const void* q, const void* k, const void* vhat, float scale, int 
   unsigned g;
   AttnArgs a = attn_args(s, scale, causal, efq_params{0.0f, 1.0f}, half, g);
   a.spread = 0;   // several candidates are more than the chip holds at once
-  RhoCand cand;
+  RhoArgs cand;
+  cand.o_ref = o_ref;
+  cand.part = part;
   for (int i = 0; i < kRhoCand; ++i) {
     const int c = c0 + (i < n ? i : 0);
     cand.tau[i] = taus[c / nh];
@@ -2313,14 +2800,14 @@ int launch_rho(const void* q, const void* k, const void* vhat, float scale, int 
     const hipError_t e = raise_lds<decltype(kernel)::value>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(decltype(kernel)::value, dim3(g, n), dim3(threads), lds, st, q, k,
-                       (const uint8_t*)vhat, o_ref, a, cand, part);
+                       (const uint8_t*)vhat, (float*)nullptr, a, cand);
     return hipGetLastError();
   };
   auto pick = [&](auto d, auto c) {
     constexpr int D = decltype(d)::value;
     constexpr bool C = decltype(c)::value;
-    return half ? launch(KernelPtr<attn_rho_kernel<kHWaves, D, C>>{}, 64 * kHWaves, SmemH<D>::kTotal)
-                : launch(KernelPtr<attn_rho_kernel<kPPWaves, D, C>>{}, kPPThreads, SmemPP<D>::kTotal);
+    return half ? launch(KernelPtr<attn_pp_kernel<D, EFQ_PGEN_EFQ, C, false, false, kHWaves, true>>{}, 64 * kHWaves, SmemH<D>::kTotal)
+                : launch(KernelPtr<attn_pp_kernel<D, EFQ_PGEN_EFQ, C, false, false, kPPWaves, true>>{}, kPPThreads, SmemPP<D>::kTotal);
   };
   hipError_t e;
   if (s->head_dim == 64) e = causal ? pick(IC<64>{}, std::true_type{}) : pick(IC<64>{}, std::false_type{});
@@ -2365,7 +2852,15 @@ size_t efq_vhat_scale_offset(const efq_shape* s) {
   return vhat_scale_offset(s);
 }
 
-size_t efq_attn_workspace_bytes(const efq_shape* s) { return efq_vhat_bytes(s); }
+size_t efq_attn_split_bytes(const efq_shape* s, int qk8) {
+  if (validate_shape(s, 0) != EFQ_OK) return 0;
+  return split_bytes(s, qk8 != 0);
+}
+
+size_t efq_attn_workspace_bytes(const efq_shape* s) {
+  if (validate_shape(s, 0) != EFQ_OK) return 0;
+  return vhat_bytes(s) + split_bytes(s, false);
+}
 
 int efq_quant_v_mxfp4(const void* v, const efq_shape* s, void* vhat, size_t vhat_nbytes,
                       efq_stream_t stream) {
@@ -2382,6 +2877,12 @@ int efq_quant_v_mxfp4(const void* v, const efq_shape* s, void* vhat, size_t vhat
 int efq_attn_fwd_vhat(const void* q, const void* k, const void* vhat, size_t vhat_nbytes,
                       float scale, int causal, int kind, efq_params p, float* out,
                       const efq_shape* s, efq_stream_t stream) {
+  return efq_attn_fwd_vhat_ws(q, k, vhat, vhat_nbytes, scale, causal, kind, p, out, s, nullptr, 0, stream);
+}
+
+int efq_attn_fwd_vhat_ws(const void* q, const void* k, const void* vhat, size_t vhat_nbytes,
+                         float scale, int causal, int kind, efq_params p, float* out,
+                         const efq_shape* s, void* ws, size_t ws_bytes, efq_stream_t stream) {
   int rc = validate_shape(s, causal);
   if (rc) return rc;
   if (!q || !k || !vhat || !out) return fail(EFQ_EINVAL, "null pointer");
@@ -2390,9 +2891,11 @@ int efq_attn_fwd_vhat(const void* q, const void* k, const void* vhat, size_t vha
   if ((rc = check_kind(kind, true)) || (rc = check_params(p)) || (rc = check_scale(scale))) return rc;
   if (vhat_nbytes < vhat_bytes(s))
     return fail(EFQ_EWORKSPACE, "vhat needs %zu bytes, got %zu", vhat_bytes(s), vhat_nbytes);
+  if (ws_bytes != 0 && !ws) return fail(EFQ_EWORKSPACE, "workspace is NULL");
+  if (ws && !aligned16(ws)) return fail(EFQ_EINVAL, "workspace must be 16-byte aligned");
   if ((rc = check_device())) return rc;
-  return launch_attn(q, k, vhat, scale, causal, kind, p, out, s, (hipStream_t)stream, nullptr,
-                     nullptr, nullptr, nullptr);
+  return launch_attn_ws(q, k, vhat, scale, causal, kind, p, out, s, ws, ws_bytes, (hipStream_t)stream,
+                        false);
 }
 
 int efq_attn_fwd_ex(const void* q, const void* k, const void* v, float scale, int causal, int kind,
@@ -2411,13 +2914,16 @@ int efq_attn_fwd_ex(const void* q, const void* k, const void* v, float scale, in
   if ((rc = check_device())) return rc;
   hipStream_t st = (hipStream_t)stream;
   void* buf = ws;
+  size_t have = ws_bytes;
   if (ws_bytes == 0) {
-    hipError_t e = hipMallocAsync(&buf, need, st);
-    if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", need, hipGetErrorString(e));
+    have = need + (causal ? 0 : split_bytes(s, false));
+    hipError_t e = hipMallocAsync(&buf, have, st);
+    if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", have, hipGetErrorString(e));
   }
   rc = launch_vquant(v, s, buf, st);
   if (rc == EFQ_OK)
-    rc = launch_attn(q, k, buf, scale, causal, kind, p, out, s, st, nullptr, nullptr, nullptr, nullptr);
+    rc = launch_attn_ws(q, k, buf, scale, causal, kind, p, out, s, (uint8_t*)buf + need, have - need, st,
+                        false);
   if (ws_bytes == 0) {
     hipError_t e = hipFreeAsync(buf, st);
     if (rc == EFQ_OK && e != hipSuccess) rc = fail(EFQ_EHIP, "hipFreeAsync: %s", hipGetErrorString(e));
@@ -2479,7 +2985,8 @@ int efq_attn_fwd_noalloc(const void* q, const void* k, const void* v, float scal
   // nothing left by an earlier call needs clearing
   rc = launch_vquant(v, s, buf, st);
   if (rc == EFQ_OK)
-    rc = launch_attn(q, k, buf, scale, causal, kind, p, out, s, st, nullptr, nullptr, nullptr, nullptr);
+    rc = launch_attn_ws(q, k, buf, scale, causal, kind, p, out, s, (uint8_t*)buf + need,
+                        EFQ_NOALLOC_SCRATCH_BYTES - need, st, false);
   return rc;
 }
 
@@ -2552,12 +3059,22 @@ static int check_qk8_args(const void* qhat, size_t qhat_nbytes, const void* khat
 int efq_attn_fwd_qk8(const void* qhat, size_t qhat_nbytes, const void* khat, size_t khat_nbytes,
                      const void* vhat, size_t vhat_nbytes, float scale, int causal, int kind,
                      efq_params p, float* out, const efq_shape* s, efq_stream_t stream) {
+  return efq_attn_fwd_qk8_ws(qhat, qhat_nbytes, khat, khat_nbytes, vhat, vhat_nbytes, scale, causal, kind,
+                             p, out, s, nullptr, 0, stream);
+}
+
+int efq_attn_fwd_qk8_ws(const void* qhat, size_t qhat_nbytes, const void* khat, size_t khat_nbytes,
+                        const void* vhat, size_t vhat_nbytes, float scale, int causal, int kind,
+                        efq_params p, float* out, const efq_shape* s, void* ws, size_t ws_bytes,
+                        efq_stream_t stream) {
   int rc = check_qk8_args(qhat, qhat_nbytes, khat, khat_nbytes, vhat, vhat_nbytes, scale, causal,
                           kind, true, p, out, s);
   if (rc) return rc;
+  if (ws_bytes != 0 && !ws) return fail(EFQ_EWORKSPACE, "workspace is NULL");
+  if (ws && !aligned16(ws)) return fail(EFQ_EINVAL, "workspace must be 16-byte aligned");
   if ((rc = check_device())) return rc;
-  return launch_attn(qhat, khat, vhat, scale, causal, kind, p, out, s, (hipStream_t)stream,
-                     nullptr, nullptr, nullptr, nullptr, true);
+  return launch_attn_ws(qhat, khat, vhat, scale, causal, kind, p, out, s, ws, ws_bytes,
+                        (hipStream_t)stream, true);
 }
 
 int efq_attn_fwd_qk8_dump(const void* qhat, size_t qhat_nbytes, const void* khat,
@@ -2587,7 +3104,7 @@ int efq_attn_fwd_qk8_dump(const void* qhat, size_t qhat_nbytes, const void* khat
 size_t efq_attn_lowbit_workspace_bytes(const efq_shape* s) {
   if (validate_shape(s, 0) != EFQ_OK) return 0;
   return round256(q8_bytes(qhat_rows(s), s->head_dim)) +
-         round256(q8_bytes(khat_rows(s), s->head_dim)) + vhat_bytes(s);
+         round256(q8_bytes(khat_rows(s), s->head_dim)) + vhat_bytes(s) + split_bytes(s, true);
 }
 
 int efq_attn_fwd_lowbit_ex(const void* q, const void* k, const void* v, float scale, int causal,
@@ -2608,9 +3125,11 @@ int efq_attn_fwd_lowbit_ex(const void* q, const void* k, const void* v, float sc
   if ((rc = check_device())) return rc;
   hipStream_t st = (hipStream_t)stream;
   void* buf = ws;
+  size_t have = ws_bytes;
   if (ws_bytes == 0) {
-    hipError_t e = hipMallocAsync(&buf, need, st);
-    if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", need, hipGetErrorString(e));
+    have = need + (causal ? 0 : split_bytes(s, true));
+    hipError_t e = hipMallocAsync(&buf, have, st);
+    if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", have, hipGetErrorString(e));
   }
   uint8_t* qh = (uint8_t*)buf;
   uint8_t* kh = qh + nq;
@@ -2619,8 +3138,8 @@ int efq_attn_fwd_lowbit_ex(const void* q, const void* k, const void* v, float sc
   if (rc == EFQ_OK) rc = launch_q8(k, s->batch, s->seq_k, s->heads_kv, s->head_dim, kh, st);
   if (rc == EFQ_OK) rc = launch_vquant(v, s, vh, st);
   if (rc == EFQ_OK)
-    rc = launch_attn(qh, kh, vh, scale, causal, kind, p, out, s, st, nullptr, nullptr, nullptr,
-                     nullptr, true);
+    rc = launch_attn_ws(qh, kh, vh, scale, causal, kind, p, out, s, (uint8_t*)buf + need, have - need, st,
+                        true);
   if (ws_bytes == 0) {
     hipError_t e = hipFreeAsync(buf, st);
     if (rc == EFQ_OK && e != hipSuccess) rc = fail(EFQ_EHIP, "hipFreeAsync: %s", hipGetErrorString(e));

@@ -107,7 +107,7 @@ def stats(trace_dir: str, out: str, workload: str, command: str):
         import bench
         grid = str(_grid_items(workload))
         efq = [ds for (n, g), ds in groups.items()
-               if n == "attn_pp_kernel<128, 0, true, false, false>" and g == grid]
+               if n == "attn_pp_kernel<128, 0, true, false, false, 8, false>" and g == grid]
         if efq:
             ds = efq[0]
             fh.write(f"# bf16 EFQ attention kernel at the {workload} launch configuration "
@@ -161,9 +161,9 @@ def counters(dirs, out: str, workload: str, command: str):
     simds, xcds = 1024, 8
     from paper_2609_09721_amd import inputs
     pairs = inputs.WORKLOADS[workload].pairs()
-    kinds = {"attn_pp_kernel<128, 0, true, false, false>": "efq",
-             "attn_pp_kernel<128, 1, true, false, false>": "expq",
-             "attn_pp_kernel<128, 3, true, false, false>": "noop"}
+    kinds = {"attn_pp_kernel<128, 0, true, false, false, 8, false>": "efq",
+             "attn_pp_kernel<128, 1, true, false, false, 8, false>": "expq",
+             "attn_pp_kernel<128, 3, true, false, false, 8, false>": "noop"}
     with open(out, "w") as fh:
         fh.write(f"# matrix-core and VALU activity of the fused attention kernel, {workload}\n")
         fh.write(f"# command (from the repository root, TMPDIR=/tmp), one run per counter pass:\n")
