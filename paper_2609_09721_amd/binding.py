@@ -106,7 +106,8 @@ def _check(status: int):
 
 def _stream(stream=None):
     if stream is None:
-        stream = torch.cuda.current_stream()
+        # the handle itself: building a Stream object costs 3 us a call
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
     return ctypes.c_void_p(stream.cuda_stream)
 
 
@@ -146,6 +147,17 @@ def _scratch(nbytes: int, device, stream=None) -> Optional[torch.Tensor]:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
     with torch.cuda.stream(stream):
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
+
+
+def _workspace(q, sh: Shape, causal, qk8: bool, workspace, stream):
+    """(workspace tensor or None, its bytes) of a whole call.  The caller's, or
+    one from torch's allocator, which keeps freed blocks: the library's own
+    stream-ordered allocation maps and unmaps device memory on every call."""
+    if workspace is None:
+        size = lib().efq_attn_lowbit_workspace_bytes if qk8 else (
+            lib().efq_vhat_bytes if causal else lib().efq_attn_workspace_bytes)
+        workspace = _scratch(int(size(ctypes.byref(sh))), q.device, stream)
+    return workspace, 0 if workspace is None else workspace.numel() * workspace.element_size()
 
 
 def _split_scratch(shape: Shape, causal, qk8: bool, device, stream):
@@ -206,10 +218,10 @@ def attn_fwd(q, k, v, scale: Optional[float] = None, causal: bool = False, kind=
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws_n = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws, ws_n = _workspace(q, sh, causal, False, workspace, stream)
     _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), kind,
-                                 _params(kind, params), _ptr(out), ctypes.byref(sh),
-                                 _ptr(workspace), ws_n, _stream(stream)))
+                                 _params(kind, params), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
+                                 _stream(stream)))
     return out
 
 
@@ -235,8 +247,10 @@ def efq_attn_fwd(q, k, v, scale=None, causal=False, out=None, stream=None):
     sh = shape_of(q, k)
     scale = q.shape[-1] ** -0.5 if scale is None else scale
     out = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    _check(lib().efq_attn_fwd(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), _ptr(out),
-                              ctypes.byref(sh), _stream(stream)))
+    ws, ws_n = _workspace(q, sh, causal, False, None, stream)
+    _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), PGEN_EFQ,
+                                 Params(*PARAMS_MEAN), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
+                                 _stream(stream)))
     return out
 
 
@@ -245,8 +259,10 @@ def efq_attn_fwd_expq(q, k, v, scale=None, causal=False, out=None, stream=None):
     sh = shape_of(q, k)
     scale = q.shape[-1] ** -0.5 if scale is None else scale
     out = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    _check(lib().efq_attn_fwd_expq(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal),
-                                   _ptr(out), ctypes.byref(sh), _stream(stream)))
+    ws, ws_n = _workspace(q, sh, causal, False, None, stream)
+    _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), PGEN_EXPQ,
+                                 Params(*PARAMS_MEAN), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
+                                 _stream(stream)))
     return out
 
 
@@ -338,10 +354,10 @@ def attn_fwd_lowbit(q, k, v, scale: Optional[float] = None, causal: bool = False
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws_n = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws, ws_n = _workspace(q, sh, causal, True, workspace, stream)
     _check(lib().efq_attn_fwd_lowbit_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), kind,
-                                        _params(kind, params), _ptr(out), ctypes.byref(sh),
-                                        _ptr(workspace), ws_n, _stream(stream)))
+                                        _params(kind, params), _ptr(out), ctypes.byref(sh), _ptr(ws),
+                                        ws_n, _stream(stream)))
     return out
 
 

@@ -144,3 +144,26 @@ def test_entry_points_streams_and_capture(B):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(got, ref) and torch.equal(out, ref), i
+
+
+@pytest.mark.gpu
+def test_default_workspace(B):
+    """Without a workspace the binding takes one from torch's allocator: calls
+    in flight on two streams, and the size following the shape."""
+    side = torch.cuda.Stream()
+    for b, s, hq, hkv, D, causal in ((1, 256, 1, 1, 64, False), (2, 700, 8, 2, 128, True), (1, 65, 4, 4, 64, True)):
+        q, k, v = _inputs(b, s, s, hq, hkv, D)
+        sh = B.shape_of(q, k)
+        ws = torch.empty(B.vhat_bytes(sh), dtype=torch.uint8, device="cuda")
+        wl = torch.empty(B.lowbit_workspace_bytes(sh), dtype=torch.uint8, device="cuda")
+        for kind, call in (("efq", B.efq_attn_fwd), ("expq", B.efq_attn_fwd_expq)):
+            ref = B.attn_fwd(q, k, v, causal=causal, kind=kind, workspace=ws)
+            low = B.attn_fwd_lowbit(q, k, v, causal=causal, kind=kind, workspace=wl)
+            torch.cuda.synchronize()
+            for _ in range(4):
+                on_side = call(q, k, v, causal=causal, stream=side, out=torch.empty_like(ref))
+                assert torch.equal(call(q, k, v, causal=causal), ref)
+                assert torch.equal(B.attn_fwd(q, k, v, causal=causal, kind=kind), ref)
+                assert torch.equal(B.attn_fwd_lowbit(q, k, v, causal=causal, kind=kind), low)
+                side.synchronize()
+                assert torch.equal(on_side, ref)
