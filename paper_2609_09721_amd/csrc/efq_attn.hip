@@ -574,6 +574,7 @@ struct AttnArgs {
   int sq_pad, sk_pad;
   size_t q8_soff, k8_soff;
   int spread;         // 1: pair long and short work items (map_work)
+  int o_rows;         // 1: half workgroups store O as whole rows, through LDS
 };
 
 // LDS layout.  A K tile is stored in the order the bf16 MFMA reads its A
@@ -1448,7 +1449,12 @@ constexpr int kHK = kHP + 1;               // K ring depth
 constexpr int kHV = kHP + 2;               // V~ ring depth
 template <int D, bool Q8 = false>
 using SmemH = Smem<D, kHK, kHV, Q8, false>;
-static_assert(2 * SmemH<128>::kTotal <= 160 * 1024 && 2 * SmemH<128, true>::kTotal <= 160 * 1024,
+// LDS of a half workgroup: the rings, or at the end its O rows
+template <int D, bool Q8>
+constexpr int half_lds() {
+  return std::max(SmemH<D, Q8>::kTotal, kHWaves * kWaveQ * D * 4);
+}
+static_assert(2 * half_lds<128, false>() <= 160 * 1024 && 2 * half_lds<128, true>() <= 160 * 1024,
               "two half workgroups exceed the LDS of a CU");
 
 // The schedule of a wave of a half workgroup.  Iteration j runs M(j) (with
@@ -1501,6 +1507,70 @@ __device__ __forceinline__ void half_schedule(PPWave<D, KIND, false, Q8, false>&
     w.template mphase<false, true, false>(T, kbuf0, kr, vop, kp, a, 0, 0, sb0, sb1, sa0, sa1);
   }
   for (int t = T; t < ntiles; ++t) end();
+}
+
+// Q rows and O rows of a half workgroup's wave pass through LDS, so that its
+// global loads and stores cover whole rows (1 KB of 2 to 8 rows an
+// instruction); in the operand layout an instruction touches 32 rows, 32
+// bytes each, and the address unit takes a cycle per row: 20 such
+// instructions a wave before the first tile kept it busy for 4000 to 7000
+// cycles.  16-byte chunk c of row r sits in slot c ^ (r mod 16) of its row
+// (r / 2 mod 8 for the 8 chunks of a bf16 D = 64 row), so that the reads and
+// writes along a column hit different banks.  Kernel time before
+// and after: 8 prompts of 333 tokens 25.9 -> 23.9 us (O direct 24.1), 32760 x
+// 512 keys 253.6 -> 232.6 (Q only 244.5, O only 236.3), x 128 keys 167.6 ->
+// 141.5.
+template <int D>
+__device__ __forceinline__ int q_swizzle(int row) {
+  return D == 128 ? row & 15 : (row >> 1) & 7;
+}
+
+// The wave's 32 rows from q_wave0 (past Sq: row Sq - 1) into LDS at qb.
+template <int D>
+__device__ __forceinline__ void half_issue_q(const unsigned short* __restrict__ q, long stride, int q_wave0,
+                                             int Sq, int lane, uint8_t* qb) {
+  constexpr int C = D / 8, RPI = 64 / C;   // chunks a row, rows an instruction
+#pragma unroll
+  for (int i = 0; i < kWaveQ / RPI; ++i) {
+    const int row = i * RPI + lane / C;
+    const unsigned short* p =
+        q + min(q_wave0 + row, Sq - 1) * stride + ((lane % C) ^ q_swizzle<D>(row)) * 8;
+    __builtin_amdgcn_global_load_lds((__attribute__((address_space(1))) const void*)p,
+                                     (__attribute__((address_space(3))) void*)(qb + i * 1024), 16, 0, 0);
+  }
+}
+
+template <int D>
+__device__ __forceinline__ void half_read_q(const uint8_t* qb, int lane, bf16x8* r) {
+  const int row = lane & 31;
+  const uint8_t* p = qb + row * (D * 2);
+  const int x = q_swizzle<D>(row) ^ (lane >> 5);
+#pragma unroll
+  for (int kk = 0; kk < D / 16; ++kk) r[kk] = *(const bf16x8*)(p + ((2 * kk) ^ x) * 16);
+}
+
+// The wave's 32 x D outputs (accumulators times rl) as rows: f(row, d, v) for
+// four outputs from column d of row `row`, whole rows of lanes at a time; ob:
+// 128 D bytes of LDS of the wave's own.
+template <int D, typename F>
+__device__ __forceinline__ void half_rows(const f32x16* oacc, float rl, int lane, uint8_t* ob, F&& f) {
+  constexpr int C = D / 4, RPI = 64 / C;
+  const int x = (lane & 15) ^ (lane >> 5);
+  uint8_t* const wp = ob + (lane & 31) * (D * 4);
+#pragma unroll
+  for (int s = 0; s < D / 32; ++s)
+#pragma unroll
+    for (int r4 = 0; r4 < 4; ++r4)
+      *(f32x4*)(wp + ((8 * s + 2 * r4) ^ x) * 16) =
+          f32x4{oacc[s][4 * r4] * rl, oacc[s][4 * r4 + 1] * rl, oacc[s][4 * r4 + 2] * rl, oacc[s][4 * r4 + 3] * rl};
+  // a wave's LDS operations complete in order
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+#pragma unroll
+  for (int i = 0; i < 32 / RPI; ++i) {
+    const int row = i * RPI + lane / C;
+    f(row, ((lane % C) ^ (row & 15)) * 4, *(const f32x4*)(ob + i * 1024 + lane * 16));
+  }
 }
 
 constexpr int kRhoCand = 64;
@@ -1560,6 +1630,11 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
     if constexpr (D == 128) raw = *(const unsigned*)sp;
     else raw = *(const unsigned short*)sp;
     w.qo.sc = lane_scales<D>(raw, w.half);
+  } else if constexpr (!kPair) {
+    // whole rows to LDS (K slots 1 and 2, tile 1 comes later); the operands
+    // are read once they have landed
+    half_issue_q<D>((const unsigned short*)q + ((long)b * a.Sq * a.Hq + hq) * D, (long)a.Hq * D, q_wave0,
+                    a.Sq, w.lane, smem + Sm::kK + wave * (kWaveQ * D * 2));
   } else {
     const unsigned short* qp =
         (const unsigned short*)q + (((long)b * a.Sq + q_load) * a.Hq + hq) * D + w.half * 8;
@@ -1655,11 +1730,19 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
     }
   };
   if constexpr (!kPair) {
-    // prologue: tiles 0 .. P-1; tile 0 resident, the others in flight
+    // prologue: tiles 0 .. P-1; tile 0 resident, the others in flight.  With
+    // bf16 Q the others are issued once every wave has read its Q rows.
+    constexpr int kFirst = Q8 ? kHP : 1;
 #pragma unroll
-    for (int x = 0; x < kHP; ++x) load_tile(x, x * Sm::kK, x * Sm::kV);
-    wait_vmem_le((kHP - 1) * kLoads);
+    for (int x = 0; x < kFirst; ++x) load_tile(x, x * Sm::kK, x * Sm::kV);
+    if constexpr (!Q8) {
+      wait_vmem_le(kLoads);
+      half_read_q<D>(smem + Sm::kK + wave * (kWaveQ * D * 2), w.lane, w.qo.r);
+    }
+    wait_vmem_le((kFirst - 1) * kLoads);
     __syncthreads();
+#pragma unroll
+    for (int x = kFirst; x < kHP; ++x) load_tile(x, x * Sm::kK, x * Sm::kV);
     int sx = kHP;
     int skofs = (kHP % kHK) * Sm::kK, svofs = (kHP % kHV) * Sm::kV;
     auto stream = [&]() {
@@ -1719,9 +1802,25 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
   // residual range [log 3/4, log 3/2) can produce; the row is then 0.
   const float l = w.lacc[0];
   const float rl = l > 0.0f ? 1.0f / l : 0.0f;
+  uint8_t* const ob = smem + wave * (kWaveQ * D * 4);   // half workgroup: O rows
+  const bool o_rows = !kPair && (RHO || a.o_rows);
+  if (o_rows) __syncthreads();                          // every wave is done with the rings
   if constexpr (RHO) {
     double d2 = 0.0, r2 = 0.0;
-    if (w.my_q < a.Sq) {
+    auto add = [&](float o, float r) {
+      const double d = (double)o - (double)r;
+      d2 += d * d;
+      r2 += (double)r * (double)r;
+    };
+    if constexpr (!kPair) {
+      half_rows<D>(w.oacc, rl, w.lane, ob, [&](int row, int d, const f32x4& o) {
+        if (q_wave0 + row < a.Sq) {
+          const f32x4 v = *(const f32x4*)(rho.o_ref + (((long)b * a.Sq + q_wave0 + row) * a.Hq + hq) * D + d);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) add(o[i], v[i]);
+        }
+      });
+    } else if (w.my_q < a.Sq) {
       const float* rp = rho.o_ref + (((long)b * a.Sq + w.my_q) * a.Hq + hq) * D;
 #pragma unroll
       for (int s = 0; s < NS; ++s) {
@@ -1729,11 +1828,7 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
         for (int r4 = 0; r4 < 4; ++r4) {
           const f32x4 v = *(const f32x4*)(rp + s * 32 + 8 * r4 + 4 * w.half);
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            const double o = w.oacc[s][4 * r4 + i] * rl, d = o - (double)v[i];
-            d2 += d * d;
-            r2 += (double)v[i] * (double)v[i];
-          }
+          for (int i = 0; i < 4; ++i) add(w.oacc[s][4 * r4 + i] * rl, v[i]);
         }
       }
     }
@@ -1755,6 +1850,11 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
       for (int i = 0; i < NW; ++i) t += red[2 * i + threadIdx.x];
       rho.part[2 * ((long)blockIdx.y * gridDim.x + blockIdx.x) + threadIdx.x] = t;
     }
+  } else if (o_rows) {
+    half_rows<D>(w.oacc, rl, w.lane, ob, [&](int row, int d, const f32x4& o) {
+      if (q_wave0 + row < a.Sq)
+        *(f32x4*)(out + (((long)b * a.Sq + q_wave0 + row) * a.Hq + hq) * D + d) = o;
+    });
   } else if (w.my_q < a.Sq) {
     float* op = out + (((long)b * a.Sq + w.my_q) * a.Hq + hq) * D;
 #pragma unroll
@@ -2465,7 +2565,7 @@ hipError_t launch_attn_t(const void* q, const void* k, const void* vhat, float* 
     return hipGetLastError();
   };
   if constexpr (HALF)
-    return launch(KernelPtr<attn_pp_kernel<D, KIND, CAUSAL, false, Q8, kHWaves, false>>{}, 64 * kHWaves, SmemH<D, Q8>::kTotal);
+    return launch(KernelPtr<attn_pp_kernel<D, KIND, CAUSAL, false, Q8, kHWaves, false>>{}, 64 * kHWaves, half_lds<D, Q8>());
   else
     return launch(KernelPtr<attn_pp_kernel<D, KIND, CAUSAL, DUMP, Q8, kPPWaves, false>>{}, kPPThreads,
                   SmemPP<D, Q8>::kTotal);
@@ -2583,6 +2683,13 @@ AttnArgs attn_args(const efq_shape* s, float scale, int causal, efq_params p, bo
   a.spread = half && causal && total <= 2 * kCUs && (long)a.B * a.Hq % 8 == 0 ? 1 : 0;
   a.sq_pad = (int)pad64(s->seq_q);
   a.sk_pad = (int)pad64(s->seq_k);
+  // A grid with more half workgroups than the CUs hold is bound by how fast
+  // they follow one another; a smaller one by one workgroup's own latency,
+  // which the pass through LDS and its barrier lengthen (512 tokens, 32 heads:
+  // 12.7 us without, 13.1 with; 32760 x 512, 24 heads: 244.5 / 232.6).
+  // With many keys the store is a small part, and direct is as fast (4096
+  // tokens, MXFP8, LUT: 83.4 / 84.5).
+  a.o_rows = total > 2 * kCUs && s->seq_k <= 1536;
   a.q8_soff = q8_scale_offset(qhat_rows(s), s->head_dim);
   a.k8_soff = q8_scale_offset(khat_rows(s), s->head_dim);
   grid = (unsigned)total;
@@ -2806,7 +2913,7 @@ int launch_rho(const void* q, const void* k, const void* vhat, float scale, int 
   auto pick = [&](auto d, auto c) {
     constexpr int D = decltype(d)::value;
     constexpr bool C = decltype(c)::value;
-    return half ? launch(KernelPtr<attn_pp_kernel<D, EFQ_PGEN_EFQ, C, false, false, kHWaves, true>>{}, 64 * kHWaves, SmemH<D>::kTotal)
+    return half ? launch(KernelPtr<attn_pp_kernel<D, EFQ_PGEN_EFQ, C, false, false, kHWaves, true>>{}, 64 * kHWaves, half_lds<D, false>())
                 : launch(KernelPtr<attn_pp_kernel<D, EFQ_PGEN_EFQ, C, false, false, kPPWaves, true>>{}, kPPThreads, SmemPP<D>::kTotal);
   };
   hipError_t e;

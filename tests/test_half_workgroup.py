@@ -68,6 +68,8 @@ SHAPES = [  # batch, seq_q, seq_k, heads, head_dim, causal: all inside use_half
     (1, 1, 1, (2, 1), 64, False), (1, 1, 700, (4, 4), 128, False), (2, 127, 65, (8, 2), 128, False),
     (1, 128, 128, (8, 8), 64, True), (1, 129, 129, (8, 2), 128, True), (3, 300, 300, (8, 8), 128, True),
     (1, 600, 449, (3, 1), 64, False), (1, 1037, 1037, (16, 2), 128, True),
+    # more workgroups than the chip holds: O leaves as whole rows, through LDS
+    (9, 257, 257, (20, 4), 64, True), (9, 130, 100, (32, 8), 128, False),
 ]
 
 
