@@ -4,6 +4,7 @@
 //   vquant_kernel      V (bf16) -> MXFP4 V~ in the FP4 matrix-core operand
 //                      order (HBM-bound pre-pass, once per call).
 //   mxfp8_kernel       Q, K (bf16) -> MXFP8 Q^, K^ for the low-bit Q K^T.
+//   lowbit_quant_kernel  both, for Q, K and V of one call in one launch.
 //   attn_pp_kernel     FlashAttention-style forward (Alg. 2 of the paper):
 //                      S^T = K Q^T on bf16 (or block-scaled FP8) MFMA, the
 //                      probability stage on the VALU (Alg. 1 for EFQ;
@@ -436,13 +437,14 @@ __device__ __forceinline__ void vq_pairs(unsigned (&words)[4], const unsigned (&
 
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, unsigned bytes);
 template <bool BUF>
-__global__ __launch_bounds__(256) void vquant_kernel(const unsigned short* __restrict__ v,
-                                                     uint8_t* __restrict__ vhat, VqArgs a) {
+__device__ __forceinline__ void vquant_block(const unsigned short* __restrict__ v,
+                                             uint8_t* __restrict__ vhat, const VqArgs& a,
+                                             unsigned block) {
   // thread index: 32-bit with buffer loads (V below 2 GiB, so fewer than
   // 2^31 threads), which keeps the divisions short
   typedef typename std::conditional<BUF, unsigned, unsigned long>::type IDX;
   const int D2 = a.D >> 1;   // 32 or 64
-  const IDX tid = (IDX)blockIdx.x * blockDim.x + threadIdx.x;
+  const IDX tid = (IDX)block * 256 + threadIdx.x;
   const IDX total = (IDX)a.B * a.H * a.nb * D2;
   if (tid >= total) return;
   const int dp = (int)(tid % D2);
@@ -499,6 +501,12 @@ __global__ __launch_bounds__(256) void vquant_kernel(const unsigned short* __res
   }
 }
 
+template <bool BUF>
+__global__ __launch_bounds__(256) void vquant_kernel(const unsigned short* __restrict__ v,
+                                                     uint8_t* __restrict__ vhat, VqArgs a) {
+  vquant_block<BUF>(v, vhat, a, blockIdx.x);
+}
+
 // ------------------------------------------------ MXFP8 Q / K quantiser
 // Low-bit Q K^T: Q and K as MXFP8 under the OCP microscaling rule, per row
 // and 32 consecutive head-dim elements: E8M0 exponent k = floor(log2 amax)
@@ -518,10 +526,10 @@ struct Q8Args {
 // IDX: the integer type of the thread and row indices (32-bit whenever the
 // thread count fits, which keeps the divisions short).
 template <typename IDX>
-__global__ __launch_bounds__(256) void mxfp8_kernel(const unsigned short* __restrict__ x,
-                                                    uint8_t* __restrict__ y, Q8Args a) {
+__device__ __forceinline__ void mxfp8_block(const unsigned short* __restrict__ x,
+                                            uint8_t* __restrict__ y, const Q8Args& a, unsigned block) {
   const int parts = a.D / 8;   // 8 or 16
-  const IDX n = (IDX)blockIdx.x * 256 + threadIdx.x;
+  const IDX n = (IDX)block * 256 + threadIdx.x;
   const IDX row = n / parts;
   const int part = (int)(n % parts);
   if (row >= (IDX)a.B * a.H * a.s_pad) return;   // whole rows, so whole 4-lane groups
@@ -554,6 +562,33 @@ __global__ __launch_bounds__(256) void mxfp8_kernel(const unsigned short* __rest
   const unsigned w[2] = {__builtin_bit_cast(unsigned, w0), __builtin_bit_cast(unsigned, w1)};
   *(uint2*)(y + row * a.D + part * 8) = make_uint2(w[0], w[1]);
   if ((part & 3) == 0) y[a.soff + row * (a.D / 32) + (part >> 2)] = (uint8_t)(k + 127);
+}
+
+template <typename IDX>
+__global__ __launch_bounds__(256) void mxfp8_kernel(const unsigned short* __restrict__ x,
+                                                    uint8_t* __restrict__ y, Q8Args a) {
+  mxfp8_block<IDX>(x, y, a, blockIdx.x);
+}
+
+// The quantisers of one call in one launch: with V, nv workgroups of V (the
+// longest first), then nq of Q, then those of K.  HBM bound, like its parts;
+// on a short prompt each of three launches was mostly its start and its tail:
+// a low-bit call on 4096 tokens (32/8 heads, D 128) 99.2 -> 96.2 us.  V's
+// part takes 76 registers, which leaves the others six waves a SIMD where
+// they had eight: 5 % slower on 65537 tokens, so long calls take V apart.
+struct QuantArgs {
+  const unsigned short *q, *k, *v;
+  uint8_t *qhat, *khat, *vhat;
+  Q8Args qa, ka;
+  VqArgs va;
+  unsigned nv, nq;
+};
+template <bool V>
+__global__ __launch_bounds__(256) void lowbit_quant_kernel(QuantArgs a) {
+  const unsigned n = blockIdx.x;
+  if (V && n < a.nv) vquant_block<true>(a.v, a.vhat, a.va, n);
+  else if (n < a.nv + a.nq) mxfp8_block<unsigned>(a.q, a.qhat, a.qa, n - a.nv);
+  else mxfp8_block<unsigned>(a.k, a.khat, a.ka, n - a.nv - a.nq);
 }
 
 // ------------------------------------------------------ fused attention
@@ -2509,7 +2544,7 @@ size_t vhat_bytes(const efq_shape* s) {
   return vhat_scale_offset(s) + ((sc + 255) & ~(size_t)255);
 }
 
-int launch_vquant(const void* v, const efq_shape* s, void* vhat, hipStream_t st) {
+VqArgs vq_args(const efq_shape* s) {
   VqArgs a;
   a.B = s->batch;
   a.S = s->seq_k;
@@ -2517,10 +2552,15 @@ int launch_vquant(const void* v, const efq_shape* s, void* vhat, hipStream_t st)
   a.D = s->head_dim;
   a.nb = (int)padded_blocks(s->seq_k);
   a.scale_off = vhat_scale_offset(s);
-  long total = (long)a.B * a.H * a.nb * (a.D / 2);
-  long grid = (total + 255) / 256;
   const size_t vb = (size_t)a.B * a.S * a.H * a.D * 2;
   a.vbytes = vb < ((size_t)1 << 31) ? (unsigned)vb : 0u;
+  return a;
+}
+long vq_blocks(const VqArgs& a) { return ((long)a.B * a.H * a.nb * (a.D / 2) + 255) / 256; }
+
+int launch_vquant(const void* v, const efq_shape* s, void* vhat, hipStream_t st) {
+  const VqArgs a = vq_args(s);
+  const long grid = vq_blocks(a);
   if (a.vbytes)
     hipLaunchKernelGGL(vquant_kernel<true>, dim3((unsigned)grid), dim3(256), 0, st,
                        (const unsigned short*)v, (uint8_t*)vhat, a);
@@ -2606,16 +2646,21 @@ size_t q8_bytes(long rows, int D) { return q8_scale_offset(rows, D) + round256((
 long qhat_rows(const efq_shape* s) { return (long)s->batch * s->heads_q * pad64(s->seq_q); }
 long khat_rows(const efq_shape* s) { return (long)s->batch * s->heads_kv * pad64(s->seq_k); }
 
-int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st) {
+Q8Args q8_args(int B, int S, int H, int D) {
   Q8Args a;
   a.B = B;
   a.S = S;
   a.H = H;
   a.D = D;
   a.s_pad = (int)pad64(S);
-  const long rows = (long)B * H * a.s_pad;
-  a.soff = q8_scale_offset(rows, D);
-  const long threads = rows * (D / 8);
+  a.soff = q8_scale_offset((long)B * H * a.s_pad, D);
+  return a;
+}
+long q8_threads(const Q8Args& a) { return (long)a.B * a.H * a.s_pad * (a.D / 8); }
+
+int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st) {
+  const Q8Args a = q8_args(B, S, H, D);
+  const long threads = q8_threads(a);
   const unsigned grid = (unsigned)((threads + 255) / 256);
   if (threads + 256 < ((long)1 << 32))
     hipLaunchKernelGGL(mxfp8_kernel<unsigned>, dim3(grid), dim3(256), 0, st,
@@ -2720,6 +2765,41 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
   else e = q8 ? launch(IC<128>{}, std::true_type{}) : launch(IC<128>{}, std::false_type{});
   if (e != hipSuccess) return fail(EFQ_EHIP, "attention launch: %s", hipGetErrorString(e));
   return EFQ_OK;
+}
+
+// Q^ and K^, and V~ where vhat is given.  One launch for Q and K where their
+// thread indices fit 32 bits, with V on short calls (at lowbit_quant_kernel).
+int launch_lowbit_quant(const void* q, const void* k, const void* v, const efq_shape* s, void* qhat,
+                        void* khat, void* vhat, hipStream_t st) {
+  QuantArgs a;
+  a.q = (const unsigned short*)q;
+  a.k = (const unsigned short*)k;
+  a.v = (const unsigned short*)v;
+  a.qhat = (uint8_t*)qhat;
+  a.khat = (uint8_t*)khat;
+  a.vhat = (uint8_t*)vhat;
+  a.qa = q8_args(s->batch, s->seq_q, s->heads_q, s->head_dim);
+  a.ka = q8_args(s->batch, s->seq_k, s->heads_kv, s->head_dim);
+  a.va = vq_args(s);
+  const long tq = q8_threads(a.qa), tk = q8_threads(a.ka), lim = ((long)1 << 32) - 256;
+  const long nq = (tq + 255) / 256, nk = (tk + 255) / 256;
+  const bool with_v = vhat && a.va.vbytes && nq + nk <= 16384;
+  const long nv = with_v ? vq_blocks(a.va) : 0;
+  int rc = EFQ_OK;
+  if (tq >= lim || tk >= lim || nv + nq + nk > 0x7FFFFFFFL) {
+    rc = launch_q8(q, s->batch, s->seq_q, s->heads_q, s->head_dim, qhat, st);
+    if (rc == EFQ_OK) rc = launch_q8(k, s->batch, s->seq_k, s->heads_kv, s->head_dim, khat, st);
+  } else {
+    a.nv = (unsigned)nv;
+    a.nq = (unsigned)nq;
+    const dim3 grid((unsigned)(nv + nq + nk));
+    if (with_v) hipLaunchKernelGGL(lowbit_quant_kernel<true>, grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL(lowbit_quant_kernel<false>, grid, dim3(256), 0, st, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(EFQ_EHIP, "quantiser launch: %s", hipGetErrorString(e));
+  }
+  if (rc == EFQ_OK && vhat && !with_v) rc = launch_vquant(v, s, vhat, st);
+  return rc;
 }
 
 // The key split of a shape (few queries): chunk sizes and the scratch it
@@ -3138,10 +3218,7 @@ int efq_quant_qk_mxfp8(const void* q, const void* k, const efq_shape* s, void* q
   if (qhat_nbytes < nq) return fail(EFQ_EWORKSPACE, "qhat needs %zu bytes, got %zu", nq, qhat_nbytes);
   if (khat_nbytes < nk) return fail(EFQ_EWORKSPACE, "khat needs %zu bytes, got %zu", nk, khat_nbytes);
   if ((rc = check_device())) return rc;
-  hipStream_t st = (hipStream_t)stream;
-  rc = launch_q8(q, s->batch, s->seq_q, s->heads_q, s->head_dim, qhat, st);
-  if (rc == EFQ_OK) rc = launch_q8(k, s->batch, s->seq_k, s->heads_kv, s->head_dim, khat, st);
-  return rc;
+  return launch_lowbit_quant(q, k, nullptr, s, qhat, khat, nullptr, (hipStream_t)stream);
 }
 
 static int check_qk8_args(const void* qhat, size_t qhat_nbytes, const void* khat,
@@ -3241,9 +3318,7 @@ int efq_attn_fwd_lowbit_ex(const void* q, const void* k, const void* v, float sc
   uint8_t* qh = (uint8_t*)buf;
   uint8_t* kh = qh + nq;
   uint8_t* vh = kh + nk;
-  rc = launch_q8(q, s->batch, s->seq_q, s->heads_q, s->head_dim, qh, st);
-  if (rc == EFQ_OK) rc = launch_q8(k, s->batch, s->seq_k, s->heads_kv, s->head_dim, kh, st);
-  if (rc == EFQ_OK) rc = launch_vquant(v, s, vh, st);
+  rc = launch_lowbit_quant(q, k, v, s, qh, kh, vh, st);
   if (rc == EFQ_OK)
     rc = launch_attn_ws(qh, kh, vh, scale, causal, kind, p, out, s, (uint8_t*)buf + need, have - need, st,
                         true);
