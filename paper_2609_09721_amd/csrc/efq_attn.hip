@@ -435,6 +435,28 @@ __device__ __forceinline__ void vq_pairs(unsigned (&words)[4], const unsigned (&
   }
 }
 
+// The lane's column c (0: low bf16 half, 1: high) of a 32-key block: its codes
+// in operand order, and the exponent k (floor(log2 amax) - 2, >= -127).
+__device__ __forceinline__ int vq_column(const unsigned (&raw)[32], int c, unsigned (&words)[4]) {
+  float amax = 0.f;
+#pragma unroll
+  for (int t = 0; t < 32; ++t)
+    amax = fmaxf(amax, __uint_as_float(c ? raw[t] & 0x7fff0000u : (raw[t] & 0x7fffu) << 16));
+  int k = -127;
+  if (amax > 0.f) {
+    // floor(log2 amax) from the fp32 bits (bf16 subnormals are fp32 normals)
+    const int e = (int)((__float_as_uint(amax) >> 23) & 0xFF) - 127;
+    k = e - 2 < -127 ? -127 : e - 2;
+  }
+  // keys t and t + 8 (t with bit 3 clear) share byte t & 3 of operand dword
+  // 2 ((t >> 2) & 1) + (t >> 4): key t in the low nibble (key_nibble);
+  // the conversion rounds y = v 2^-k (exact) to the nearest E2M1 value,
+  // ties to the even code, sign from the input
+  words[0] = words[1] = words[2] = words[3] = 0;
+  vq_pairs<0>(words, raw, c, k);
+  return k;
+}
+
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, unsigned bytes);
 template <bool BUF>
 __device__ __forceinline__ void vquant_block(const unsigned short* __restrict__ v,
@@ -473,28 +495,12 @@ __device__ __forceinline__ void vquant_block(const unsigned short* __restrict__ 
 #pragma unroll
     for (int t = 0; t < 32; ++t) raw[t] = t < nvalid ? p[t * stride] : 0u;
   }
-  float amax[2] = {0.f, 0.f};
-#pragma unroll
-  for (int t = 0; t < 32; ++t) {
-    amax[0] = fmaxf(amax[0], __uint_as_float((raw[t] & 0x7fffu) << 16));
-    amax[1] = fmaxf(amax[1], __uint_as_float(raw[t] & 0x7fff0000u));
-  }
   uint8_t* codes = vhat + (((long)b * a.H + g) * a.nb + blk) * a.D * 16;
   uint8_t* scales = vhat + a.scale_off + (((long)b * a.H + g) * a.nb + blk) * a.D;
 #pragma unroll
   for (int c = 0; c < 2; ++c) {
-    int k = -127;
-    if (amax[c] > 0.f) {
-      // floor(log2 amax) from the fp32 bits (bf16 subnormals are fp32 normals)
-      int e = (int)((__float_as_uint(amax[c]) >> 23) & 0xFF) - 127;
-      k = e - 2 < -127 ? -127 : e - 2;
-    }
-    // keys t and t + 8 (t with bit 3 clear) share byte t & 3 of operand dword
-    // 2 ((t >> 2) & 1) + (t >> 4): key t in the low nibble (key_nibble);
-    // the conversion rounds y = v 2^-k (exact) to the nearest E2M1 value,
-    // ties to the even code, sign from the input
-    unsigned words[4] = {0, 0, 0, 0};
-    vq_pairs<0>(words, raw, c, k);
+    unsigned words[4];
+    const int k = vq_column(raw, c, words);
     *(u32x4*)(codes + (long)(d0 + c) * 16) = u32x4{words[0], words[1], words[2], words[3]};
     const int d = d0 + c;
     scales[(d & 31) * (a.D >> 5) + (d >> 5)] = (uint8_t)(k + 127);
@@ -2116,9 +2122,50 @@ split_max_kernel(const void* __restrict__ q, const void* __restrict__ k, SplitAr
   }
 }
 
+// V of one 64-key tile, straight from bf16 (a whole call, one column tile: a
+// wave is the only reader of its tile, so V~ need not be written and read
+// back).  The lane holds the column pair (2 lane, 2 lane + 1) of the tile's
+// 64 rows; the quantised tile passes through the wave's own LDS in the layout
+// of V~.  Same arithmetic as vquant_kernel.
+template <int D>
+struct SplitV {
+  static_assert(D == 128, "64 lanes hold the columns");
+  unsigned raw[2][32];
+  // rows past Sk read the last one; quantise() zeroes them
+  __device__ __forceinline__ void read(const __amdgpu_buffer_rsrc_t& rs, int voff, int stride, int tile, int Sk) {
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk)
+#pragma unroll
+      for (int t = 0; t < 32; ++t)
+        raw[blk][t] = __builtin_amdgcn_raw_buffer_load_b32(
+            rs, voff, min(tile * kBc + blk * 32 + t, Sk - 1) * stride, 0);
+  }
+  __device__ __forceinline__ void quantise(uint8_t* vb, int tile, int Sk, int lane) {
+#pragma unroll
+    for (int blk = 0; blk < 2; ++blk) {
+      const int nvalid = Sk - tile * kBc - blk * 32;
+      if (nvalid < 32) {
+#pragma unroll
+        for (int t = 0; t < 32; ++t) raw[blk][t] = t < nvalid ? raw[blk][t] : 0u;
+      }
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        unsigned words[4];
+        const int k = vq_column(raw[blk], c, words);
+        const int d = 2 * lane + c;
+        *(u32x4*)(vb + (blk * D + d) * 16) = u32x4{words[0], words[1], words[2], words[3]};
+        vb[2 * D * 16 + blk * D + (d & 31) * (D / 32) + (d >> 5)] = (uint8_t)(k + 127);
+      }
+    }
+    // a wave's LDS operations complete in order
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
 // One wave per (batch, kv head, column tile, chunk); the last chunk of a
-// workgroup has its largest (running) maximum.
-template <int D, int KIND, bool Q8, bool KEEP>
+// workgroup has its largest (running) maximum.  RAWV: vhat is V itself (bf16).
+template <int D, int KIND, bool Q8, bool KEEP, bool RAWV>
 __global__ __attribute__((amdgpu_flat_work_group_size(64 * kSWaves, 64 * kSWaves),
                           amdgpu_waves_per_eu(2, KEEP ? 3 : 2))) void
 split_attn_kernel(const void* __restrict__ q, const void* __restrict__ k,
@@ -2126,6 +2173,8 @@ split_attn_kernel(const void* __restrict__ q, const void* __restrict__ k,
   constexpr int NS = D / 32;
   __shared__ __align__(16) float so[kSWaves][D / 16][64][4];   // scaled A of each wave, half the columns
   __shared__ float sm[kSWaves][32], sl[kSWaves][32];
+  constexpr int kVb = RAWV ? 2 * D * 16 + 2 * D : 16;
+  __shared__ __align__(16) uint8_t svb[kSWaves][kVb];               // the wave's quantised V tile
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63, half = lane >> 5;
   int w = split_work(a);
@@ -2178,7 +2227,12 @@ split_attn_kernel(const void* __restrict__ q, const void* __restrict__ k,
       else v.sv = *(const unsigned short*)(vs + (long)t * (2 * D));
     };
     VOps<D> vop;
-    read_vops(t0, vop);
+    std::conditional_t<RAWV, SplitV<128>, NoRho> rv;
+    const int vstride = a.Hkv * D * 2;
+    const __amdgpu_buffer_rsrc_t vrs =
+        make_rsrc(vhat + (long)b * a.Sk * vstride, (unsigned)a.Sk * (unsigned)vstride);
+    if constexpr (RAWV) rv.read(vrs, g * D * 2 + lane * 4, vstride, t0, a.Sk);
+    else read_vops(t0, vop);
     // the running maximum at the chunk's first key: the lane halves take
     // alternate earlier chunks
     {
@@ -2199,11 +2253,13 @@ split_attn_kernel(const void* __restrict__ q, const void* __restrict__ k,
       } else {
         split_qk<D, Q8>(kr, qo, s0, s1);
       }
-      const VOps<D> v = vop;
+      VOps<D> v = vop;
+      if constexpr (RAWV) rv.quantise(svb[wave], t, a.Sk, lane);
       if (t + 1 < t1) {
         if constexpr (KEEP) read_scores(t + 1);
         else split_read_k<D, Q8>(k, a, b, g, t + 1, lane, kr);
-        read_vops(t + 1, vop);
+        if constexpr (RAWV) rv.read(vrs, g * D * 2 + lane * 4, vstride, t + 1, a.Sk);
+        else read_vops(t + 1, vop);
       }
       if ((t + 1) * kBc > a.Sk) mask_tile(s0, s1, a.Sk - t * kBc - 4 * half);
       float pm0, pm1;
@@ -2218,8 +2274,15 @@ split_attn_kernel(const void* __restrict__ q, const void* __restrict__ k,
       pg_pairs<KIND, 0, 32>(s0, s1, pa, st);
       const PgenOut po = pg_finish<KIND>(st);
       const i32x8 b8 = i32x8{(int)po.bop[0], (int)po.bop[1], (int)po.bop[2], (int)po.bop[3], 0, 0, 0, 0};
+      if constexpr (RAWV)
+        read_v<D>(lds_at(lds_addr(svb[wave] + vop_offset<D>(lane))),
+                  lds_at(lds_addr(svb[wave] + vscale_offset<D>(lane))), v);
       pv_slabs<NS>(oacc, v, b8, po.scale_b);
       lacc = rowsum_mfma(sel, b8, lacc, po.scale_b);
+      if constexpr (RAWV) {   // the next tile overwrites the LDS after these reads
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_wave_barrier();
+      }
     }
   }
   // merge the workgroup's chunks at the maximum of its last one
@@ -2854,7 +2917,7 @@ SplitPlan split_plan(const efq_shape* s, bool q8) {
 // Scratch bytes of the split (a multiple of 256).
 size_t split_bytes(const efq_shape* s, bool q8) { return round256(split_plan(s, q8).bytes); }
 
-template <int D, bool Q8, bool KEEP>
+template <int D, bool Q8, bool KEEP, bool RAWV>
 hipError_t launch_split_t(int kind, const void* q, const void* k, const void* vhat, float* out,
                           const SplitArgs& a, hipStream_t st) {
   const unsigned bg = (unsigned)(a.B * a.Hkv);
@@ -2871,17 +2934,17 @@ hipError_t launch_split_t(int kind, const void* q, const void* k, const void* vh
   bool log2 = false;
   switch (kind) {
     case EFQ_PGEN_EFQ:
-      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EFQ, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EFQ, Q8, KEEP, RAWV>), grid, block, 0, st, q, k, v, a);
       break;
     case EFQ_PGEN_LUT:
-      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_LUT, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_LUT, Q8, KEEP, RAWV>), grid, block, 0, st, q, k, v, a);
       break;
     case EFQ_PGEN_EXPQ:
-      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EXPQ, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EXPQ, Q8, KEEP, RAWV>), grid, block, 0, st, q, k, v, a);
       log2 = true;
       break;
     case EFQ_PGEN_EXPQ6:
-      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EXPQ6, Q8, KEEP>), grid, block, 0, st, q, k, v, a);
+      hipLaunchKernelGGL((split_attn_kernel<D, EFQ_PGEN_EXPQ6, Q8, KEEP, RAWV>), grid, block, 0, st, q, k, v, a);
       log2 = true;
       break;
     default:
@@ -2893,7 +2956,8 @@ hipError_t launch_split_t(int kind, const void* q, const void* k, const void* vh
 }
 
 int launch_split(const void* q, const void* k, const void* vhat, float scale, int kind, efq_params p,
-                 float* out, const efq_shape* s, const SplitPlan& pl, void* ws, hipStream_t st, bool q8) {
+                 float* out, const efq_shape* s, const SplitPlan& pl, void* ws, hipStream_t st, bool q8,
+                 bool rawv = false) {
   SplitArgs a;
   a.B = s->batch;
   a.Sq = s->seq_q;
@@ -2923,8 +2987,10 @@ int launch_split(const void* q, const void* k, const void* vhat, float scale, in
   auto launch = [&](auto d, auto is_q8) {
     constexpr int D = decltype(d)::value;
     constexpr bool Q8 = decltype(is_q8)::value;
-    return pl.scores ? launch_split_t<D, Q8, true>(kind, q, k, vhat, out, a, st)
-                     : launch_split_t<D, Q8, false>(kind, q, k, vhat, out, a, st);
+    if constexpr (D == 128 && !Q8)
+      if (rawv) return launch_split_t<D, Q8, true, true>(kind, q, k, vhat, out, a, st);
+    return pl.scores ? launch_split_t<D, Q8, true, false>(kind, q, k, vhat, out, a, st)
+                     : launch_split_t<D, Q8, false, false>(kind, q, k, vhat, out, a, st);
   };
   hipError_t e;
   if (s->head_dim == 64) e = q8 ? launch(IC<64>{}, std::true_type{}) : launch(IC<64>{}, std::false_type{});
@@ -2945,6 +3011,23 @@ int launch_attn_ws(const void* q, const void* k, const void* vhat, float scale, 
   }
   return launch_attn(q, k, vhat, scale, causal, kind, p, out, s, st, nullptr, nullptr, nullptr,
                      nullptr, q8);
+}
+
+// A whole bf16 call: V~ into vhat, then the attention, with split scratch ws.
+// Where the split has one column tile (a generation step) and D = 128, it
+// quantises V itself and vhat stays unused: V is read once, 8 x 1 query
+// against 6001 keys 63.4 -> 55.2 us.
+int launch_attn_v(const void* q, const void* k, const void* v, float scale, int causal, int kind,
+                  efq_params p, float* out, const efq_shape* s, void* vhat, void* ws, size_t ws_bytes,
+                  hipStream_t st) {
+  if (!causal && kind != EFQ_PGEN_NOOP && s->head_dim == 128) {
+    const SplitPlan pl = split_plan(s, false);
+    if (pl.bytes && pl.scores && ws && ws_bytes >= pl.bytes)
+      return launch_split(q, k, v, scale, kind, p, out, s, pl, ws, st, false, true);
+  }
+  const int rc = launch_vquant(v, s, vhat, st);
+  if (rc != EFQ_OK) return rc;
+  return launch_attn_ws(q, k, vhat, scale, causal, kind, p, out, s, ws, ws_bytes, st, false);
 }
 
 int check_kind(int kind, bool allow_noop) {
@@ -3107,10 +3190,7 @@ int efq_attn_fwd_ex(const void* q, const void* k, const void* v, float scale, in
     hipError_t e = hipMallocAsync(&buf, have, st);
     if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", have, hipGetErrorString(e));
   }
-  rc = launch_vquant(v, s, buf, st);
-  if (rc == EFQ_OK)
-    rc = launch_attn_ws(q, k, buf, scale, causal, kind, p, out, s, (uint8_t*)buf + need, have - need, st,
-                        false);
+  rc = launch_attn_v(q, k, v, scale, causal, kind, p, out, s, buf, (uint8_t*)buf + need, have - need, st);
   if (ws_bytes == 0) {
     hipError_t e = hipFreeAsync(buf, st);
     if (rc == EFQ_OK && e != hipSuccess) rc = fail(EFQ_EHIP, "hipFreeAsync: %s", hipGetErrorString(e));
@@ -3170,11 +3250,8 @@ int efq_attn_fwd_noalloc(const void* q, const void* k, const void* v, float scal
   hipStream_t st = (hipStream_t)stream;
   // the V quantiser writes every byte of V~ the attention kernel reads, so
   // nothing left by an earlier call needs clearing
-  rc = launch_vquant(v, s, buf, st);
-  if (rc == EFQ_OK)
-    rc = launch_attn_ws(q, k, buf, scale, causal, kind, p, out, s, (uint8_t*)buf + need,
-                        EFQ_NOALLOC_SCRATCH_BYTES - need, st, false);
-  return rc;
+  return launch_attn_v(q, k, v, scale, causal, kind, p, out, s, buf, (uint8_t*)buf + need,
+                       EFQ_NOALLOC_SCRATCH_BYTES - need, st);
 }
 
 int efq_attn_fwd(const void* q, const void* k, const void* v, float scale, int causal, float* out,

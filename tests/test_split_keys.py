@@ -167,3 +167,18 @@ def test_default_workspace(B):
                 assert torch.equal(B.attn_fwd_lowbit(q, k, v, causal=causal, kind=kind), low)
                 side.synchronize()
                 assert torch.equal(on_side, ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", [(1, 1, 1025, 32, 8, 128), (2, 5, 2111, 6, 3, 128), (1, 16, 3000, 4, 4, 128)])
+@pytest.mark.parametrize("kind", ["efq", "lut", "expq", "expq6"])
+def test_whole_call_quantises_v_in_place(B, shape, kind):
+    """The whole call's split reads V itself; the values are those of V~."""
+    b, sq, sk, hq, hkv, D = shape
+    print(f"[split v] {shape} {kind}", flush=True)
+    assert split_bytes(B, shape) > 0
+    q, k, v = _inputs(b, sq, sk, hq, hkv, D)
+    v[:, : sk // 2] *= 2.0 ** -9
+    v[:, -33:] = 0                       # blocks without a value, and the ragged end
+    assert torch.equal(B.attn_fwd(q, k, v, kind=kind),
+                       B.attn_fwd_vhat(q, k, B.quant_v(v, seq_q=sq, heads_q=hq), kind=kind))
