@@ -156,14 +156,20 @@ def _workspace(q, sh: Shape, causal, qk8: bool, workspace, stream):
     if workspace is None:
         size = lib().efq_attn_lowbit_workspace_bytes if qk8 else (
             lib().efq_vhat_bytes if causal else lib().efq_attn_workspace_bytes)
-        workspace = _scratch(int(size(ctypes.byref(sh))), q.device, stream)
+        try:
+            workspace = _scratch(int(size(ctypes.byref(sh))), q.device, stream)
+        except torch.OutOfMemoryError:
+            workspace = None            # the library then tries an allocation of its own
     return workspace, 0 if workspace is None else workspace.numel() * workspace.element_size()
 
 
 def _split_scratch(shape: Shape, causal, qk8: bool, device, stream):
     """(scratch or None, bytes) of the key split that few queries run by."""
     n = 0 if causal else int(lib().efq_attn_split_bytes(ctypes.byref(shape), int(qk8)))
-    return _scratch(n, device, stream), n
+    try:
+        return _scratch(n, device, stream), n
+    except torch.OutOfMemoryError:      # without scratch the unsplit kernels run
+        return None, 0
 
 
 def vhat_bytes(shape: Shape) -> int:

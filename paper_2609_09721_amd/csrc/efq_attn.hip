@@ -1937,6 +1937,7 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
 constexpr int kSWaves = 4;                 // chunks per workgroup
 constexpr int kSRows = 128;                // most rows (queries x group) taken
 constexpr int kSItems = 2048;              // waves the chip holds at two per SIMD
+constexpr double kSplitScores = 256 << 20; // most bytes of scores kept (the rest of the scratch is < 16 MB)
 
 struct SplitArgs {
   int B, Sq, Sk, Hq, Hkv;
@@ -2896,7 +2897,7 @@ SplitPlan split_plan(const efq_shape* s, bool q8) {
   const double kb = (double)bg * s->seq_k * D * (q8 ? 33.0 / 32 : 2.0);
   const double vb = (double)bg * s->seq_k * D * (17.0 / 32);
   const double sb = (double)bg * p.ntiles * kBc * 4 * p.R;
-  p.scores = p.CT == 1 && 2 * sb <= kb;
+  p.scores = p.CT == 1 && 2 * sb <= kb && sb <= kSplitScores;
   const double wgs = (double)s->batch * s->heads_q * ((s->seq_q + 127) / 128);
   const double rounds = wgs <= kCUs ? 1.0 : 0.8 * wgs / kCUs;
   const double unsplit = 6 + std::max(p.ntiles * (D == 128 ? 0.75 : 0.65) * rounds, (kb + vb) / 5e6);
@@ -3188,6 +3189,11 @@ int efq_attn_fwd_ex(const void* q, const void* k, const void* v, float scale, in
   if (ws_bytes == 0) {
     have = need + (causal ? 0 : split_bytes(s, false));
     hipError_t e = hipMallocAsync(&buf, have, st);
+    if (e != hipSuccess && have > need) {   // unsplit, then
+      (void)hipGetLastError();
+      have = need;
+      e = hipMallocAsync(&buf, have, st);
+    }
     if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", have, hipGetErrorString(e));
   }
   rc = launch_attn_v(q, k, v, scale, causal, kind, p, out, s, buf, (uint8_t*)buf + need, have - need, st);
@@ -3390,6 +3396,11 @@ int efq_attn_fwd_lowbit_ex(const void* q, const void* k, const void* v, float sc
   if (ws_bytes == 0) {
     have = need + (causal ? 0 : split_bytes(s, true));
     hipError_t e = hipMallocAsync(&buf, have, st);
+    if (e != hipSuccess && have > need) {   // unsplit, then
+      (void)hipGetLastError();
+      have = need;
+      e = hipMallocAsync(&buf, have, st);
+    }
     if (e != hipSuccess) return fail(EFQ_EHIP, "hipMallocAsync(%zu): %s", have, hipGetErrorString(e));
   }
   uint8_t* qh = (uint8_t*)buf;

@@ -41,6 +41,8 @@ def test_scratch_sizes(B):
         assert lib.efq_attn_lowbit_workspace_bytes(ctypes.byref(sh)) == (
             lib.efq_qhat_bytes(ctypes.byref(sh)) + lib.efq_khat_bytes(ctypes.byref(sh)) + B.vhat_bytes(sh) + q8)
     assert split_bytes(B, (1, 1, 4096, 32, 8, 96)) == 0
+    # the scratch stays bounded: no scores beyond 256 MiB
+    assert max(split_bytes(B, (64, sq, 120000, 64, 8, 128), q) for sq in (1, 2, 4, 16) for q in (0, 1)) < 300 << 20
 
 
 def test_scratch_arguments(B):
