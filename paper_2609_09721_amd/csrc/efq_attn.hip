@@ -2749,6 +2749,9 @@ int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st
 //  - MXFP8 Q K^T and causal: a tile reads half the K bytes, so the doubled
 //    reads cost little and the even spread of the causal lengths wins (4096
 //    83.9 / 80.1, 6000 168.9 / 163.9, but 16384 1021 / 1060).
+//  - non-causal, up to 1536 keys, and a grid of one to two rounds of the
+//    eight-wave kernel, whose second round is part empty (4 x 1500, 12 heads,
+//    D 64: 49.6 / 45.5; 8000 x 1024, 24 heads, in between: 96.2 / 94.7).
 // Elsewhere the eight-wave kernel is as fast or faster (4096 tokens causal
 // 107.5 / 111.3, 7000 x 7000 24 heads 415 / 449).
 bool use_half(const efq_shape* s, int causal, bool q8) {
