@@ -526,6 +526,18 @@ struct Q8Args {
   size_t soff;
 };
 
+// Byte offsets in Q^ (K^) of the codes of part `part` (8 elements) of a row,
+// and of its block's scale from the scales' start: 64-bit whatever the type of
+// the row index, since the codes pass 4 GiB long before the thread index does.
+template <typename IDX>
+__host__ __device__ __forceinline__ size_t q8_code_at(IDX row, int D, int part) {
+  return (size_t)row * D + part * 8;
+}
+template <typename IDX>
+__host__ __device__ __forceinline__ size_t q8_scale_at(IDX row, int D, int part) {
+  return (size_t)row * (D / 32) + (part >> 2);
+}
+
 // One thread per 8 elements (4 threads per 32-element block, lanes 4i..4i+3);
 // the rounding is the hardware E4M3 conversion (two elements per
 // instruction) of |x| 2^-k clamped to 448, with the input's sign.
@@ -566,8 +578,8 @@ __device__ __forceinline__ void mxfp8_block(const unsigned short* __restrict__ x
   w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, y2(2, 0), y2(2, 1), 1.0f, false);
   w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, y2(3, 0), y2(3, 1), 1.0f, true);
   const unsigned w[2] = {__builtin_bit_cast(unsigned, w0), __builtin_bit_cast(unsigned, w1)};
-  *(uint2*)(y + row * a.D + part * 8) = make_uint2(w[0], w[1]);
-  if ((part & 3) == 0) y[a.soff + row * (a.D / 32) + (part >> 2)] = (uint8_t)(k + 127);
+  *(uint2*)(y + q8_code_at(row, a.D, part)) = make_uint2(w[0], w[1]);
+  if ((part & 3) == 0) y[a.soff + q8_scale_at(row, a.D, part)] = (uint8_t)(k + 127);
 }
 
 template <typename IDX>
@@ -2722,6 +2734,10 @@ Q8Args q8_args(int B, int S, int H, int D) {
 }
 long q8_threads(const Q8Args& a) { return (long)a.B * a.H * a.s_pad * (a.D / 8); }
 
+// Whether a launch of this many workgroups of 256 threads is within the 32
+// bits that HIP takes for the threads of a launch.
+bool fits_launch(long workgroups) { return workgroups < (1L << 24); }
+
 int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st) {
   const Q8Args a = q8_args(B, S, H, D);
   const long threads = q8_threads(a);
@@ -2835,7 +2851,8 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
 }
 
 // Q^ and K^, and V~ where vhat is given.  One launch for Q and K where their
-// thread indices fit 32 bits, with V on short calls (at lowbit_quant_kernel).
+// thread indices and their threads together fit 32 bits, with V on short calls
+// (at lowbit_quant_kernel).
 int launch_lowbit_quant(const void* q, const void* k, const void* v, const efq_shape* s, void* qhat,
                         void* khat, void* vhat, hipStream_t st) {
   QuantArgs a;
@@ -2853,7 +2870,7 @@ int launch_lowbit_quant(const void* q, const void* k, const void* v, const efq_s
   const bool with_v = vhat && a.va.vbytes && nq + nk <= 16384;
   const long nv = with_v ? vq_blocks(a.va) : 0;
   int rc = EFQ_OK;
-  if (tq >= lim || tk >= lim || nv + nq + nk > 0x7FFFFFFFL) {
+  if (tq >= lim || tk >= lim || !fits_launch(nv + nq + nk)) {
     rc = launch_q8(q, s->batch, s->seq_q, s->heads_q, s->head_dim, qhat, st);
     if (rc == EFQ_OK) rc = launch_q8(k, s->batch, s->seq_k, s->heads_kv, s->head_dim, khat, st);
   } else {
