@@ -63,6 +63,7 @@ constexpr float kLn6 = 1.79175946922805500081f;      // log 6, Eq. (z-def)
 constexpr int kWaveQ = 32;     // queries per wave (MFMA N)
 constexpr int kBc = 64;        // keys per tile (two 32-key microscaling blocks)
 constexpr int kXcdCUs = 32;    // compute units of one of the 8 XCDs
+constexpr int kCUs = 8 * kXcdCUs;
 
 // C16 fold table of EFQ-Softmax-LUT (Sec. II-D) as bytes: byte j of the
 // 16-byte table (little-endian dwords kC16T0..3) is C16[j].
@@ -626,7 +627,7 @@ struct AttnArgs {
   // MXFP8 Q^ / K^ (low-bit Q K^T): padded rows per head, scale offsets
   int sq_pad, sk_pad;
   size_t q8_soff, k8_soff;
-  int spread;         // 1: pair long and short work items (map_work)
+  int spread;         // order of the work items (map_work)
   int o_rows;         // 1: half workgroups store O as whole rows, through LDS
 };
 
@@ -851,11 +852,19 @@ __device__ __forceinline__ void wait_vmem_le(int n) {
 // of work items.  Consecutive work items are the query heads of one GQA group
 // at one query tile, then the next tile, so the workgroups that stream the
 // same key/value tiles run side by side on one XCD and share its L2.  Query
-// tiles run longest first.  With `spread` (a causal grid of half workgroups
-// that is resident at once, two on a CU) an XCD's items are ordered by length
-// over all its heads and the second 32 (one per CU) reversed, so that a
-// long workgroup shares its CU with a short one: 2 prompts of 1024 tokens
-// 28.2 -> 24.9 us, one of 2048 40.0 -> 38.4 us.
+// tiles run longest first.  The half workgroups of a causal grid have two more
+// orders (`spread`, work_order), since there the length of an item decides:
+//  1: an XCD's items by length over all its heads, the second 32 (one per CU)
+//     reversed, so that a long workgroup shares its CU with a short one: 2
+//     prompts of 1024 tokens 28.2 -> 24.9 us, one of 2048 40.0 -> 38.4 us;
+//  2: all items by length over all heads, in the order they are handed out,
+//     the second 256 reversed where the grid is resident at once.  Where the
+//     heads do not divide evenly over the XCDs, whole heads leave some XCDs
+//     with the long tiles of one more head, and where the workgroups do not
+//     the last head's long tiles start last.  12 heads, EFQ, eight-wave kernel
+//     / half workgroups head by head / in this order (us): 4096 tokens, D 128
+//     69.4 / 70.6 / 61.7; 6000 tokens, D 64, MXFP8 66.3 / 70.7 / 65.0; 11 x 600
+//     tokens, D 64 23.5 / 20.1 / 17.3.
 template <bool SPREAD>
 __device__ __forceinline__ void map_work(const AttnArgs& a, int& b, int& hq, int& qt) {
   const int n = blockIdx.x;
@@ -863,10 +872,17 @@ __device__ __forceinline__ void map_work(const AttnArgs& a, int& b, int& hq, int
   int w = n;
   if (a.xcd_remap) w = (n & 7) * (total >> 3) + (n >> 3);
   if (SPREAD && a.spread) {
-    const int items = total >> 3, heads = items / a.nqt;   // of one XCD
-    int i = n >> 3;
-    if (i >= kXcdCUs) i = kXcdCUs + items - 1 - i;
-    const int bh = (n & 7) * heads + i % heads;
+    int i = n, heads = total / a.nqt, first = 0;           // of all XCDs
+    if (a.spread == 2) {
+      if (total <= 2 * kCUs && i >= kCUs) i = kCUs + total - 1 - i;
+    } else {
+      const int items = total >> 3;                        // of one XCD
+      heads = items / a.nqt;
+      first = (n & 7) * heads;
+      i = n >> 3;
+      if (i >= kXcdCUs) i = kXcdCUs + items - 1 - i;
+    }
+    const int bh = first + i % heads;
     qt = a.nqt - 1 - i / heads;
     hq = bh % a.Hq;
     b = bh / a.Hq;
@@ -2549,7 +2565,6 @@ __global__ __launch_bounds__(256) void rho_final_kernel(const double* __restrict
 // ================================================================ host side
 constexpr int kQTile = kPPBr;   // queries per workgroup of the launched kernel
 constexpr int kMaxDevices = 64; // device indices the library accepts
-constexpr int kCUs = 8 * kXcdCUs;
 
 thread_local char g_msg[512] = "ok";
 
@@ -2787,6 +2802,14 @@ bool rho_half(const efq_shape* s, int causal) {
   return s->seq_q <= kQTile / 2 || s->seq_k <= (causal ? 1024 : 768);
 }
 
+// The order (map_work) of a causal grid of half workgroups: by length where it
+// is resident at once, two on a CU, or where its workgroups do not divide over
+// the XCDs; else head by head, whose K and V~ then stay in the XCD's L2.
+int work_order(long total, long heads) {
+  if (total > 2 * kCUs) return total % 8 ? 2 : 0;
+  return heads % 8 ? 2 : 1;
+}
+
 // Arguments and grid size of an attention launch (half: the half-workgroup
 // kernel), without the dump buffers.
 AttnArgs attn_args(const efq_shape* s, float scale, int causal, efq_params p, bool half, unsigned& grid) {
@@ -2808,7 +2831,7 @@ AttnArgs attn_args(const efq_shape* s, float scale, int causal, efq_params p, bo
   a.nblk = (s->seq_k + 31) / 32;
   const long total = (long)a.B * a.Hq * a.nqt;
   a.xcd_remap = (total % 8 == 0) ? 1 : 0;
-  a.spread = half && causal && total <= 2 * kCUs && (long)a.B * a.Hq % 8 == 0 ? 1 : 0;
+  a.spread = half && causal ? work_order(total, (long)a.B * a.Hq) : 0;
   a.sq_pad = (int)pad64(s->seq_q);
   a.sk_pad = (int)pad64(s->seq_k);
   // A grid with more half workgroups than the CUs hold is bound by how fast

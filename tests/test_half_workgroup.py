@@ -4,6 +4,7 @@ output against the eight-wave kernel's.  Both run the same tile code in the
 same order per query, so the outputs must be equal bit for bit; the entry
 point that records the probability stage always runs the eight-wave kernel."""
 import os
+import subprocess
 
 import pytest
 import torch
@@ -56,6 +57,63 @@ def test_spread_order_visits_every_item_once(B, Hq, Hkv, nqt):
     assert all(0 <= b < B and 0 <= q < nqt for b, _, q in seen)
 
 
+def _function(src, head):
+    at = src.index(head)
+    return src[at: src.index("\n}\n", at) + 3]
+
+
+# batch, heads, key/value heads, query tiles: every order, on both sides of 256
+# and 512 workgroups, heads and workgroups that divide by the 8 XCDs and not
+GRIDS = [(1, 32, 8, 16), (1, 24, 24, 12), (1, 12, 12, 21), (1, 12, 12, 32), (3, 12, 12, 9), (1, 1, 1, 257),
+         (1, 2, 2, 235), (1, 20, 4, 19), (1, 12, 12, 47), (11, 12, 12, 5), (1, 4, 4, 128), (1, 32, 8, 17),
+         (1, 9, 3, 1), (7, 1, 1, 3)]
+
+
+def test_every_work_order_visits_every_item_once(tmp_path):
+    """map_work and work_order themselves, compiled for the host: a bijection
+    of the grid onto (batch, head, tile); workgroups that are handed out
+    together with the longest are the shortest."""
+    src = open(SRC).read()
+    prog = tmp_path / "order.cpp"
+    prog.write_text("""#include <cstdio>
+#include <cstdlib>
+#define __device__
+#define __forceinline__ inline
+constexpr int kXcdCUs = 32, kCUs = 8 * kXcdCUs;
+struct { int x; } blockIdx, gridDim;
+struct AttnArgs { int B, Hq, Hkv, nqt, xcd_remap, spread; };
+template <bool SPREAD>
+""" + _function(src, "__device__ __forceinline__ void map_work(") + _function(src, "int work_order(") + """
+int main(int, char** v) {
+  AttnArgs a;
+  a.B = atoi(v[1]); a.Hq = atoi(v[2]); a.Hkv = atoi(v[3]); a.nqt = atoi(v[4]);
+  gridDim.x = a.B * a.Hq * a.nqt;
+  a.xcd_remap = gridDim.x % 8 == 0;
+  a.spread = atoi(v[5]) ? work_order(gridDim.x, (long)a.B * a.Hq) : 0;
+  for (blockIdx.x = 0; blockIdx.x < gridDim.x; ++blockIdx.x) {
+    int b, hq, qt;
+    map_work<true>(a, b, hq, qt);
+    printf("%d %d %d\\n", b, hq, qt);
+  }
+}
+""")
+    exe = tmp_path / "order"
+    subprocess.run(["g++", "-O1", "-o", str(exe), str(prog)], check=True)
+    for grid in GRIDS:
+        b, hq, _, nqt = grid
+        total = b * hq * nqt
+        for causal in (0, 1):
+            out = subprocess.run([str(exe), *map(str, grid), str(causal)], capture_output=True, text=True, check=True)
+            items = [tuple(map(int, line.split())) for line in out.stdout.splitlines()]
+            assert sorted(items) == [(x, y, z) for x in range(b) for y in range(hq) for z in range(nqt)], grid
+            if causal and (total <= 512 and b * hq % 8 or total > 512 and total % 8):
+                by_length = sorted((z for _, _, z in items), reverse=True)
+                order = [z for _, _, z in items]
+                if total <= 512:
+                    order[256:] = order[256:][::-1]
+                assert order == by_length, grid
+
+
 @pytest.fixture(scope="module")
 def B():
     from paper_2609_09721_amd import binding
@@ -68,6 +126,10 @@ SHAPES = [  # batch, seq_q, seq_k, heads, head_dim, causal: all inside use_half
     (1, 1, 1, (2, 1), 64, False), (1, 1, 700, (4, 4), 128, False), (2, 127, 65, (8, 2), 128, False),
     (1, 128, 128, (8, 8), 64, True), (1, 129, 129, (8, 2), 128, True), (3, 300, 300, (8, 8), 128, True),
     (1, 600, 449, (3, 1), 64, False), (1, 1037, 1037, (16, 2), 128, True),
+    # causal, by length: 257 to 512 workgroups, heads that divide over the XCDs
+    # and that do not, and more workgroups than are resident, not a multiple of 8
+    (1, 2048, 2048, (32, 8), 128, True), (1, 1500, 1500, (24, 8), 64, True), (3, 1100, 1100, (12, 4), 128, True),
+    (1, 2500, 2500, (20, 4), 64, True), (11, 600, 600, (12, 4), 64, True),
     # more workgroups than the chip holds: O leaves as whole rows, through LDS
     (9, 257, 257, (20, 4), 64, True), (9, 130, 100, (32, 8), 128, False),
 ]
