@@ -2783,9 +2783,14 @@ int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st
 //  - non-causal, up to 1536 keys, and a grid of one to two rounds of the
 //    eight-wave kernel, whose second round is part empty (4 x 1500, 12 heads,
 //    D 64: 49.6 / 45.5; 8000 x 1024, 24 heads, in between: 96.2 / 94.7).
+//    With 129 to 255 eight-wave workgroups, one round, some CUs get two half
+//    workgroups and take as long as the eight waves do: what is left is the
+//    stage itself, and with more than 1024 keys EFQ is 1-4 % faster there, the
+//    LUT and, at D = 128, exp-then-quantize 1-4 % slower (1500 x 1500, 24 heads,
+//    D 128: EFQ 34.5 / 34.0, LUT 37.7 / 38.6, exp 40.9 / 42.2).
 // Elsewhere the eight-wave kernel is as fast or faster (4096 tokens causal
 // 107.5 / 111.3, 7000 x 7000 24 heads 415 / 449).
-bool use_half(const efq_shape* s, int causal, bool q8) {
+bool use_half(const efq_shape* s, int causal, int kind, bool q8) {
 #if EFQ_PHASE_STAMPS
   return false;   // the stamped build records the eight-wave kernel
 #endif
@@ -2793,7 +2798,11 @@ bool use_half(const efq_shape* s, int causal, bool q8) {
   if (s->seq_q <= kQTile / 2) return true;   // at most half of the waves have queries
   if (s->seq_k <= (causal ? 1024 : 768)) return true;
   if (causal && q8 && s->seq_k <= 6144) return true;
-  return causal ? wg8 <= kCUs : s->seq_k <= 1536 && wg8 <= 2 * kCUs;
+  if (causal) return wg8 <= kCUs;
+  if (s->seq_k > 1536 || wg8 > 2 * kCUs) return false;
+  if (wg8 <= kCUs / 2 || wg8 >= kCUs) return true;
+  const bool exp = kind == EFQ_PGEN_EXPQ || kind == EFQ_PGEN_EXPQ6;
+  return s->seq_k <= 1024 || q8 || kind == EFQ_PGEN_EFQ || (exp && s->head_dim == 64);
 }
 
 // The calibration runs many candidates in one launch, so the grid is never
@@ -2852,7 +2861,7 @@ int launch_attn(const void* q, const void* k, const void* vhat, float scale, int
                 efq_params p, float* out, const efq_shape* s, hipStream_t st, uint8_t* p_codes,
                 uint8_t* p_e8m0, float* row_m, float* row_l, bool q8 = false) {
   const bool dump = p_codes != nullptr;
-  const bool half = !dump && kind != EFQ_PGEN_NOOP && use_half(s, causal, q8);
+  const bool half = !dump && kind != EFQ_PGEN_NOOP && use_half(s, causal, kind, q8);
   unsigned g;
   AttnArgs a = attn_args(s, scale, causal, p, half, g);
   a.p_codes = p_codes;
