@@ -2774,6 +2774,11 @@ int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st
 //    idle CUs or finish early ones (one prompt of 1500 / 2048 tokens, 32 heads
 //    32.8 / 28.8 and 43.8 / 38.4; 64 sequences' single queries against 4096 keys
 //    602 / 375, where seven of the eight waves have no query);
+//    Not so the cheapest stage (EFQ) on bf16 keys that no other head shares,
+//    from HBM, where a CU has no second workgroup: the two tiles this kernel has
+//    in flight hide less of the latency than the other's four (24 heads, D 128,
+//    up to 112 workgroups: 4 x 16 queries, 30000 keys 388 / 421, 10000 keys 137 /
+//    144, but 8 x 16 queries, 6678 keys 119 / 108; 12 key/value heads 389 / 398).
 //  - few keys: loads and stores around the tiles weigh most (32760 x 128 / 512 /
 //    1024 keys, 24 heads: 196 / 166, 276 / 263, 396 / 406; 8 prompts of 1024
 //    tokens 90.8 / 84.0, of 2048 277 / 288);
@@ -2795,7 +2800,10 @@ bool use_half(const efq_shape* s, int causal, int kind, bool q8) {
   return false;   // the stamped build records the eight-wave kernel
 #endif
   const long wg8 = (long)s->batch * s->heads_q * ((s->seq_q + kQTile - 1) / kQTile);
-  if (s->seq_q <= kQTile / 2) return true;   // at most half of the waves have queries
+  if (s->seq_q <= kQTile / 2) {   // at most half of the waves have queries
+    const bool far = s->heads_q == s->heads_kv && s->seq_k > 8192 && wg8 <= kCUs * 7 / 16;
+    return !(far && kind == EFQ_PGEN_EFQ && !q8 && s->head_dim == 128);
+  }
   if (s->seq_k <= (causal ? 1024 : 768)) return true;
   if (causal && q8 && s->seq_k <= 6144) return true;
   if (causal) return wg8 <= kCUs;

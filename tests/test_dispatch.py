@@ -39,6 +39,11 @@ int main(int, char** v) {
 
 
 @pytest.mark.parametrize("shape,causal,kind,q8,half", [
+    # few queries: unshared keys streamed from HBM by less than one workgroup a CU
+    ((4, 16, 30000, 24, 24, 128), 0, EFQ, 0, False), ((2, 100, 30000, 24, 24, 128), 0, EFQ, 0, False),
+    ((4, 16, 30000, 24, 24, 128), 0, LUT, 0, True), ((4, 16, 30000, 24, 24, 128), 0, EFQ, 1, True),
+    ((8, 16, 12000, 24, 24, 128), 0, EFQ, 0, True), ((4, 16, 6678, 24, 24, 128), 0, EFQ, 0, True),
+    ((4, 16, 30000, 32, 8, 128), 0, EFQ, 0, True), ((4, 16, 30000, 16, 16, 64), 0, EFQ, 0, True),
     # non-causal, one round of eight-wave workgroups that half workgroups share CUs in
     ((2, 1500, 1500, 12, 12, 64), 0, LUT, 0, False), ((2, 1500, 1500, 12, 12, 64), 0, EFQ, 0, True),
     ((2, 1500, 1500, 12, 12, 64), 0, EXPQ, 0, True), ((2, 1500, 1500, 12, 12, 64), 0, LUT, 1, True),
