@@ -2929,21 +2929,37 @@ int launch_lowbit_quant(const void* q, const void* k, const void* v, const efq_s
 // The key split of a shape (few queries): chunk sizes and the scratch it
 // needs, or bytes = 0 where the unsplit kernels take it.  The line lies where
 // two estimates (us) cross, both from timed shapes:
-//  - unsplit: a tile of keys takes a workgroup 0.75 us (0.65 at D = 64), two
-//    workgroups on a CU 1.2 us together, but no less than K and V~ at 5 TB/s;
+//  - unsplit: a tile of keys takes a workgroup 0.6 to 0.75 us; workgroups that
+//    share a CU overlap the less the more a tile reads; and no less than K and
+//    V~ at 5 TB/s;
 //  - split: three launches, and K twice (or once, with the scores stored and
-//    read back, while these are fewer bytes) and V~ at 5 TB/s, but no less
-//    than 0.9 us per tile and SIMD.
-// Measured, unsplit / split (us): one query of 32 heads against 700 keys 15.3
-// / 17.4, 4096 52 / 20, 32768 368 / 55; 16 sequences with 24 key/value heads of
-// their own against 8192 keys 255 / 467 (K read twice).
+//    read back, while these are fewer bytes) and V~ at 5 TB/s (the partial sums
+//    stay in the caches), but no less than 0.9 us per tile and SIMD;
+//  - with more than one column tile, each of them reads K again in the second
+//    pass, mostly from the caches: a chunk's tiles in turn for every round of
+//    the 512 workgroups the chip holds;
+//  - once the unsplit kernel fills the chip, only the work counts: it takes
+//    every head of a group through K on its own, the split every column tile,
+//    at 1.5 of the cost.  Without heads to share K the split gains only where
+//    (nearly) every wave of its workgroups has a chunk;
+//  - the heavier stages lengthen an unsplit tile, but hide in the split, whose
+//    waves wait for K and V~.
+// Measured, unsplit / split (us), D 128 unless noted: one query of 32 heads
+// against 700 keys 15.3 / 17.4, 4096 52 / 20, 32768 368 / 55; 16 sequences with
+// 24 key/value heads of their own against 8192 keys 255 / 467 (K read twice).
+// 32/8 heads: 4 x 32 queries, 8000 keys 101 / 68, 8 x 32 111 / 132, 8 x 24 111 /
+// 146, 64 x 32, 4096 keys 381 / 575; 12 heads, D 64, 8 x 128, 8000 keys 85 / 142.
+// One chunk, where nothing is split but a group's heads share K: 256 x 1, 4096
+// keys 1473 / 818; without heads to share it (12, D 64, MXFP8), one chunk 237 x
+// 1, 740 keys 68 / 106, five 36 x 1, 9502 keys 111 / 150, four 46 x 1, 6450
+// keys 126 / 115.
 struct SplitPlan {
   bool scores;                           // keep the scores between the passes
   int R, CT, ntiles, tpc, nch, ngrp;
   size_t cmax, part, ml, sc, bytes;      // byte offsets of the scratch parts, total
 };
 
-SplitPlan split_plan(const efq_shape* s, bool q8) {
+SplitPlan split_plan(const efq_shape* s, bool q8, int kind) {
   SplitPlan p;
   memset(&p, 0, sizeof p);
   const long R = (long)s->seq_q * (s->heads_q / s->heads_kv);
@@ -2958,14 +2974,29 @@ SplitPlan split_plan(const efq_shape* s, bool q8) {
   const double vb = (double)bg * s->seq_k * D * (17.0 / 32);
   const double sb = (double)bg * p.ntiles * kBc * 4 * p.R;
   p.scores = p.CT == 1 && 2 * sb <= kb && sb <= kSplitScores;
-  const double wgs = (double)s->batch * s->heads_q * ((s->seq_q + 127) / 128);
-  const double rounds = wgs <= kCUs ? 1.0 : 0.8 * wgs / kCUs;
-  const double unsplit = 6 + std::max(p.ntiles * (D == 128 ? 0.75 : 0.65) * rounds, (kb + vb) / 5e6);
-  const double split = 14 + std::max((kb + vb + (p.scores ? 2 * sb : kb)) / 5e6, tiles / 1024 * 0.9);
-  if (split > 0.9 * unsplit) return p;
   p.tpc = (int)std::min<double>(p.ntiles, std::ceil(tiles / kSItems));
   p.nch = (p.ntiles + p.tpc - 1) / p.tpc;
   p.ngrp = (p.nch + kSWaves - 1) / kSWaves;
+  const int G = s->heads_q / s->heads_kv;
+  const double full = (double)s->batch * s->heads_q * ((s->seq_q + 127) / 128) / kCUs;   // workgroups a CU
+  const bool big = D == 128;
+  const double once = (kb + vb) / 5e6;
+  double unsplit = p.ntiles * (big ? 0.75 : 0.65) * (full <= 1 ? 1.0 : 0.8 * full);
+  double split = std::max(once + (p.scores ? 2 * sb : kb) / 5e6, tiles / 1024 * 0.9);
+  if (14 + split > 0.9 * (6 + std::max(unsplit, once))) return p;
+  if (p.CT == 1) {
+    if (full > 1 && G == 1 && p.nch < (kind == EFQ_PGEN_EFQ ? 0.9 : 0.7) * kSWaves * p.ngrp) return p;
+  } else {
+    const double tile = big ? (q8 ? 0.64 : 0.73) : (q8 ? 0.60 : 0.62);
+    const double share = big ? (q8 ? 0.70 : 0.95) : (q8 ? 0.52 : 0.62);
+    unsplit = p.ntiles * tile * std::max(1.0, share * full);
+    split = std::max((kb * ((p.CT + 1) / 2 + 0.6 * p.CT) + vb * (0.4 + 0.6 * p.CT)) / 6.5e6,
+                     p.tpc * std::ceil((double)bg * p.CT * p.ngrp / (2 * kCUs)) *
+                         (big ? (q8 ? 2.5 : 5.0) : (q8 ? 1.35 : 2.4)));
+    if (full > 1) split = std::min(split, std::max(unsplit, once) * 1.5 * p.CT / G);
+    unsplit *= kind == EFQ_PGEN_EFQ ? 1.0 : kind == EFQ_PGEN_LUT ? 1.15 : 1.2;
+    if (14 + split > 0.95 * (6 + std::max(unsplit, once))) return p;
+  }
   if (bg * p.CT * p.ngrp > 0x7FFFFFFFL || bg * p.R > 0x7FFFFFFFL) return p;
   p.cmax = 0;
   p.part = round256((size_t)bg * p.nch * p.CT * 32 * 4);
@@ -2975,8 +3006,9 @@ SplitPlan split_plan(const efq_shape* s, bool q8) {
   return p;
 }
 
-// Scratch bytes of the split (a multiple of 256).
-size_t split_bytes(const efq_shape* s, bool q8) { return round256(split_plan(s, q8).bytes); }
+// Scratch bytes of the split (a multiple of 256), whichever stage runs: the
+// plan that splits wherever another does.
+size_t split_bytes(const efq_shape* s, bool q8) { return round256(split_plan(s, q8, EFQ_PGEN_EXPQ).bytes); }
 
 template <int D, bool Q8, bool KEEP, bool RAWV>
 hipError_t launch_split_t(int kind, const void* q, const void* k, const void* vhat, float* out,
@@ -3066,7 +3098,7 @@ int launch_attn_ws(const void* q, const void* k, const void* vhat, float scale, 
                    efq_params p, float* out, const efq_shape* s, void* ws, size_t ws_bytes,
                    hipStream_t st, bool q8) {
   if (!causal && kind != EFQ_PGEN_NOOP) {
-    const SplitPlan pl = split_plan(s, q8);
+    const SplitPlan pl = split_plan(s, q8, kind);
     if (pl.bytes && ws && ws_bytes >= pl.bytes)
       return launch_split(q, k, vhat, scale, kind, p, out, s, pl, ws, st, q8);
   }
@@ -3082,7 +3114,7 @@ int launch_attn_v(const void* q, const void* k, const void* v, float scale, int 
                   efq_params p, float* out, const efq_shape* s, void* vhat, void* ws, size_t ws_bytes,
                   hipStream_t st) {
   if (!causal && kind != EFQ_PGEN_NOOP && s->head_dim == 128) {
-    const SplitPlan pl = split_plan(s, false);
+    const SplitPlan pl = split_plan(s, false, kind);
     if (pl.bytes && pl.scores && ws && ws_bytes >= pl.bytes)
       return launch_split(q, k, v, scale, kind, p, out, s, pl, ws, st, false, true);
   }

@@ -170,7 +170,7 @@ def counters(dirs, out: str, workload: str, command: str):
         for c in command.split(" ;; "):
             fh.write(f"#   {c}\n")
         fh.write("# kernel template: <head_dim, pgen kind (0 EFQ, 1 EXPQ, 3 no-op), causal, dump, "
-                 "MXFP8 Q K^T>\n")
+                 "MXFP8 Q K^T, waves per workgroup, calibration sums>\n")
         fh.write("# cycles per XCD = GRBM_GUI_ACTIVE / 8; MFMA busy and VALU active are per SIMD "
                  "(SQ_ACTIVE_INST_VALU is in quad-cycles, summed over the SIMD's waves)\n")
         fh.write("# VALU per score: wave instructions (MFMA included) x 64 lanes / visible "

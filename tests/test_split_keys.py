@@ -75,6 +75,9 @@ def _bound(sk, v):
 SHAPES = [  # batch, seq_q, seq_k, heads, head_dim: rows 1 .. 128, one key past a tile, chunks of one tile
     (1, 1, 1025, (1, 1), 64), (1, 1, 4096, (32, 8), 128), (2, 1, 3001, (16, 1), 128), (1, 31, 2000, (4, 4), 128),
     (1, 33, 1984, (3, 3), 64), (1, 128, 2111, (2, 2), 128), (3, 8, 1601, (8, 1), 64), (1, 16, 9000, (32, 8), 128),
+    # fewer chunks than a workgroup has waves: one, two and three, with stored scores and without
+    (256, 1, 129, (32, 8), 128), (256, 1, 129, (64, 8), 64), (130, 4, 200, (64, 8), 128), (90, 2, 257, (32, 8), 64),
+    (146, 5, 94, (64, 8), 128),
 ]
 
 
