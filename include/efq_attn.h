@@ -131,8 +131,8 @@ int efq_attn_fwd_vhat(const void *q, const void *k, const void *vhat, size_t vha
  * codes, scales and row maxima are those of the unsplit kernels; the output
  * is the same sums taken in another order (fp32 rounding).
  * efq_attn_split_bytes: the scratch bytes for this shape with bf16 (qk8 == 0)
- * or MXFP8 (qk8 != 0) Q K^T, 0 where no stage runs split (the heavier stages
- * gain from it at more shapes than EFQ).
+ * or MXFP8 (qk8 != 0) Q K^T, at most 512 MiB, 0 where no stage runs split (the
+ * heavier stages gain from it at more shapes than EFQ).
  * efq_attn_fwd_vhat_ws: efq_attn_fwd_vhat with scratch (device, 16-byte
  * aligned).  Without it (ws NULL, ws_bytes 0) or with less than
  * efq_attn_split_bytes the unsplit kernels run, as in efq_attn_fwd_vhat. */

@@ -1965,7 +1965,10 @@ attn_pp_kernel(const void* __restrict__ q, const void* __restrict__ k,
 constexpr int kSWaves = 4;                 // chunks per workgroup
 constexpr int kSRows = 128;                // most rows (queries x group) taken
 constexpr int kSItems = 2048;              // waves the chip holds at two per SIMD
-constexpr double kSplitScores = 256 << 20; // most bytes of scores kept (the rest of the scratch is < 16 MB)
+// Most bytes of scratch: scores kept, and maxima and partial sums, which are
+// about the output once a (batch, kv head) has a single workgroup.
+constexpr double kSplitScores = 256 << 20;
+constexpr size_t kSplitSums = 256 << 20;
 
 struct SplitArgs {
   int B, Sq, Sk, Hq, Hkv;
@@ -2997,11 +3000,11 @@ SplitPlan split_plan(const efq_shape* s, bool q8, int kind) {
     unsplit *= kind == EFQ_PGEN_EFQ ? 1.0 : kind == EFQ_PGEN_LUT ? 1.15 : 1.2;
     if (14 + split > 0.95 * (6 + std::max(unsplit, once))) return p;
   }
-  if (bg * p.CT * p.ngrp > 0x7FFFFFFFL || bg * p.R > 0x7FFFFFFFL) return p;
   p.cmax = 0;
   p.part = round256((size_t)bg * p.nch * p.CT * 32 * 4);
   p.ml = p.part + round256((size_t)bg * p.ngrp * p.R * D * 4);
   p.sc = p.ml + round256((size_t)bg * p.ngrp * p.R * 8);
+  if (p.sc > kSplitSums) return p;   // which also keeps every launch below 2^32 threads
   p.bytes = p.sc + (p.scores ? (size_t)sb : 0);
   return p;
 }

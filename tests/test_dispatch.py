@@ -34,7 +34,7 @@ def rules(tmp_path_factory):
 #include "efq_attn.h"
 constexpr int kQTile = 256;
 size_t round256(size_t n) { return (n + 255) & ~(size_t)255; }
-""" + _constants(src, "kXcdCUs", "kCUs", "kBc", "kSWaves", "kSRows", "kSItems", "kSplitScores")
+""" + _constants(src, "kXcdCUs", "kCUs", "kBc", "kSWaves", "kSRows", "kSItems", "kSplitScores", "kSplitSums")
         + _function(src, "bool use_half(") + src[at: src.index("};", at) + 3] + _function(src, "SplitPlan split_plan(") + """
 int main(int, char** v) {
   auto n = [&](int i) { return atoi(v[i]); };
@@ -140,3 +140,20 @@ def test_shapes_of_the_split_tests_split(rules):
                 assert n > 0, (b, sq, sk, hq, hkv, D, kind, q8)
                 chunks.add(min(n, 4))
     assert chunks == {1, 2, 3, 4}
+
+
+def test_split_scratch_is_bounded(rules):
+    """256 MiB of scores and 256 MiB of maxima and partial sums; and every launch
+    of the split below 2^32 threads, whatever the batch."""
+    most = 0
+    for batch in (1, 64, 256, 1024, 4096, 16384, 1 << 17, 1 << 20, 1 << 23):
+        for sq, sk, hq, hkv, D in ((1, 4096, 32, 8, 128), (8, 1024, 32, 8, 128), (5, 100, 64, 8, 128),
+                                   (32, 4096, 32, 8, 128), (1, 120000, 64, 8, 128), (16, 700, 32, 4, 64)):
+            for q8 in (0, 1):
+                nch, n = rules((batch, sq, sk, hq, hkv, D), 0, EXPQ, q8)[1:]
+                if n:
+                    R = sq * hq // hkv
+                    wgs = batch * hkv * -(-nch // 4) * -(-R // 32)
+                    assert wgs * 256 < 1 << 32 and batch * hkv * R * D < 1 << 32
+                most = max(most, n)
+    assert 0 < most <= 512 << 20
