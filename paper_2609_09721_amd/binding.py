@@ -149,23 +149,31 @@ def _scratch(nbytes: int, device, stream=None) -> Optional[torch.Tensor]:
         return torch.empty(nbytes, dtype=torch.uint8, device=device)
 
 
-def _workspace(q, sh: Shape, causal, qk8: bool, workspace, stream):
+def _splits(causal, kind) -> bool:
+    """Whether calls of this form may run split over the keys at all."""
+    return not causal and kind != PGEN_NOOP
+
+
+def _workspace(q, sh: Shape, causal, kind, qk8: bool, workspace, stream):
     """(workspace tensor or None, its bytes) of a whole call.  The caller's, or
     one from torch's allocator, which keeps freed blocks: the library's own
     stream-ordered allocation maps and unmaps device memory on every call."""
     if workspace is None:
-        size = lib().efq_attn_lowbit_workspace_bytes if qk8 else (
-            lib().efq_vhat_bytes if causal else lib().efq_attn_workspace_bytes)
+        s, l = ctypes.byref(sh), lib()
+        if _splits(causal, kind):
+            n = l.efq_attn_lowbit_workspace_bytes(s) if qk8 else l.efq_attn_workspace_bytes(s)
+        else:
+            n = l.efq_vhat_bytes(s) + (l.efq_qhat_bytes(s) + l.efq_khat_bytes(s) if qk8 else 0)
         try:
-            workspace = _scratch(int(size(ctypes.byref(sh))), q.device, stream)
+            workspace = _scratch(int(n), q.device, stream)
         except torch.OutOfMemoryError:
             workspace = None            # the library then tries an allocation of its own
     return workspace, 0 if workspace is None else workspace.numel() * workspace.element_size()
 
 
-def _split_scratch(shape: Shape, causal, qk8: bool, device, stream):
+def _split_scratch(shape: Shape, causal, kind, qk8: bool, device, stream):
     """(scratch or None, bytes) of the key split that few queries run by."""
-    n = 0 if causal else int(lib().efq_attn_split_bytes(ctypes.byref(shape), int(qk8)))
+    n = int(lib().efq_attn_split_bytes(ctypes.byref(shape), int(qk8))) if _splits(causal, kind) else 0
     try:
         return _scratch(n, device, stream), n
     except torch.OutOfMemoryError:      # without scratch the unsplit kernels run
@@ -204,7 +212,7 @@ def attn_fwd_vhat(q, k, vhat, scale: Optional[float] = None, causal: bool = Fals
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws, ws_n = _split_scratch(sh, causal, False, q.device, stream)
+    ws, ws_n = _split_scratch(sh, causal, kind, False, q.device, stream)
     _check(lib().efq_attn_fwd_vhat_ws(_ptr(q), _ptr(k), _ptr(vhat), vhat.numel(), float(scale),
                                       int(causal), kind, _params(kind, params), _ptr(out),
                                       ctypes.byref(sh), _ptr(ws), ws_n, _stream(stream)))
@@ -224,7 +232,7 @@ def attn_fwd(q, k, v, scale: Optional[float] = None, causal: bool = False, kind=
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws, ws_n = _workspace(q, sh, causal, False, workspace, stream)
+    ws, ws_n = _workspace(q, sh, causal, kind, False, workspace, stream)
     _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), kind,
                                  _params(kind, params), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
                                  _stream(stream)))
@@ -253,7 +261,7 @@ def efq_attn_fwd(q, k, v, scale=None, causal=False, out=None, stream=None):
     sh = shape_of(q, k)
     scale = q.shape[-1] ** -0.5 if scale is None else scale
     out = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    ws, ws_n = _workspace(q, sh, causal, False, None, stream)
+    ws, ws_n = _workspace(q, sh, causal, PGEN_EFQ, False, None, stream)
     _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), PGEN_EFQ,
                                  Params(*PARAMS_MEAN), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
                                  _stream(stream)))
@@ -265,7 +273,7 @@ def efq_attn_fwd_expq(q, k, v, scale=None, causal=False, out=None, stream=None):
     sh = shape_of(q, k)
     scale = q.shape[-1] ** -0.5 if scale is None else scale
     out = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    ws, ws_n = _workspace(q, sh, causal, False, None, stream)
+    ws, ws_n = _workspace(q, sh, causal, PGEN_EXPQ, False, None, stream)
     _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), PGEN_EXPQ,
                                  Params(*PARAMS_MEAN), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
                                  _stream(stream)))
@@ -316,7 +324,7 @@ def attn_fwd_qk8(qhat, khat, vhat, shape: Shape, scale: Optional[float] = None,
     if out is None:
         out = torch.empty((shape.batch, shape.seq_q, shape.heads_q, shape.head_dim),
                           dtype=torch.float32, device=qhat.device)
-    ws, ws_n = _split_scratch(shape, causal, True, qhat.device, stream)
+    ws, ws_n = _split_scratch(shape, causal, kind, True, qhat.device, stream)
     _check(lib().efq_attn_fwd_qk8_ws(_ptr(qhat), qhat.numel(), _ptr(khat), khat.numel(), _ptr(vhat),
                                      vhat.numel(), float(scale), int(causal), kind,
                                      _params(kind, params), _ptr(out), ctypes.byref(shape), _ptr(ws),
@@ -360,7 +368,7 @@ def attn_fwd_lowbit(q, k, v, scale: Optional[float] = None, causal: bool = False
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws, ws_n = _workspace(q, sh, causal, True, workspace, stream)
+    ws, ws_n = _workspace(q, sh, causal, kind, True, workspace, stream)
     _check(lib().efq_attn_fwd_lowbit_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), kind,
                                         _params(kind, params), _ptr(out), ctypes.byref(sh), _ptr(ws),
                                         ws_n, _stream(stream)))

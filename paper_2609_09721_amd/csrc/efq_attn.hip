@@ -3282,7 +3282,7 @@ int efq_attn_fwd_ex(const void* q, const void* k, const void* v, float scale, in
   void* buf = ws;
   size_t have = ws_bytes;
   if (ws_bytes == 0) {
-    have = need + (causal ? 0 : split_bytes(s, false));
+    have = need + (causal || kind == EFQ_PGEN_NOOP ? 0 : round256(split_plan(s, false, kind).bytes));
     hipError_t e = hipMallocAsync(&buf, have, st);
     if (e != hipSuccess && have > need) {   // unsplit, then
       (void)hipGetLastError();
@@ -3489,7 +3489,7 @@ int efq_attn_fwd_lowbit_ex(const void* q, const void* k, const void* v, float sc
   void* buf = ws;
   size_t have = ws_bytes;
   if (ws_bytes == 0) {
-    have = need + (causal ? 0 : split_bytes(s, true));
+    have = need + (causal || kind == EFQ_PGEN_NOOP ? 0 : round256(split_plan(s, true, kind).bytes));
     hipError_t e = hipMallocAsync(&buf, have, st);
     if (e != hipSuccess && have > need) {   // unsplit, then
       (void)hipGetLastError();
