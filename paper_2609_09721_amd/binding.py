@@ -138,15 +138,18 @@ def _bf16(t: torch.Tensor, name: str):
         raise ValueError(f"{name} must be a contiguous bf16 CUDA tensor")
 
 
-def _scratch(nbytes: int, device, stream=None) -> Optional[torch.Tensor]:
+def _scratch(nbytes: int, stream=None) -> Optional[torch.Tensor]:
     """Scratch of one call from torch's allocator, in the memory pool of the
-    stream that uses it (so it is reused only after that work), or None."""
-    if nbytes == 0:
+    stream that uses it (so it is reused only after that work), or None.  A
+    call without a stream runs on the current device's current stream, whatever
+    device its tensors are on; a stream that is only a handle (not torch's) has
+    no pool, and gets None."""
+    if nbytes == 0 or not (stream is None or isinstance(stream, torch.cuda.Stream)):
         return None
     if stream is None:
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
     with torch.cuda.stream(stream):
-        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+        return torch.empty(nbytes, dtype=torch.uint8, device="cuda")
 
 
 def _splits(causal, kind) -> bool:
@@ -154,7 +157,7 @@ def _splits(causal, kind) -> bool:
     return not causal and kind != PGEN_NOOP
 
 
-def _workspace(q, sh: Shape, causal, kind, qk8: bool, workspace, stream):
+def _workspace(sh: Shape, causal, kind, qk8: bool, workspace, stream):
     """(workspace tensor or None, its bytes) of a whole call.  The caller's, or
     one from torch's allocator, which keeps freed blocks: the library's own
     stream-ordered allocation maps and unmaps device memory on every call."""
@@ -165,19 +168,20 @@ def _workspace(q, sh: Shape, causal, kind, qk8: bool, workspace, stream):
         else:
             n = l.efq_vhat_bytes(s) + (l.efq_qhat_bytes(s) + l.efq_khat_bytes(s) if qk8 else 0)
         try:
-            workspace = _scratch(int(n), q.device, stream)
+            workspace = _scratch(int(n), stream)
         except torch.OutOfMemoryError:
             workspace = None            # the library then tries an allocation of its own
     return workspace, 0 if workspace is None else workspace.numel() * workspace.element_size()
 
 
-def _split_scratch(shape: Shape, causal, kind, qk8: bool, device, stream):
+def _split_scratch(shape: Shape, causal, kind, qk8: bool, stream):
     """(scratch or None, bytes) of the key split that few queries run by."""
     n = int(lib().efq_attn_split_bytes(ctypes.byref(shape), int(qk8))) if _splits(causal, kind) else 0
     try:
-        return _scratch(n, device, stream), n
+        scratch = _scratch(n, stream)
     except torch.OutOfMemoryError:      # without scratch the unsplit kernels run
-        return None, 0
+        scratch = None
+    return scratch, 0 if scratch is None else n
 
 
 def vhat_bytes(shape: Shape) -> int:
@@ -212,7 +216,7 @@ def attn_fwd_vhat(q, k, vhat, scale: Optional[float] = None, causal: bool = Fals
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws, ws_n = _split_scratch(sh, causal, kind, False, q.device, stream)
+    ws, ws_n = _split_scratch(sh, causal, kind, False, stream)
     _check(lib().efq_attn_fwd_vhat_ws(_ptr(q), _ptr(k), _ptr(vhat), vhat.numel(), float(scale),
                                       int(causal), kind, _params(kind, params), _ptr(out),
                                       ctypes.byref(sh), _ptr(ws), ws_n, _stream(stream)))
@@ -232,7 +236,7 @@ def attn_fwd(q, k, v, scale: Optional[float] = None, causal: bool = False, kind=
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws, ws_n = _workspace(q, sh, causal, kind, False, workspace, stream)
+    ws, ws_n = _workspace(sh, causal, kind, False, workspace, stream)
     _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), kind,
                                  _params(kind, params), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
                                  _stream(stream)))
@@ -261,7 +265,7 @@ def efq_attn_fwd(q, k, v, scale=None, causal=False, out=None, stream=None):
     sh = shape_of(q, k)
     scale = q.shape[-1] ** -0.5 if scale is None else scale
     out = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    ws, ws_n = _workspace(q, sh, causal, PGEN_EFQ, False, None, stream)
+    ws, ws_n = _workspace(sh, causal, PGEN_EFQ, False, None, stream)
     _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), PGEN_EFQ,
                                  Params(*PARAMS_MEAN), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
                                  _stream(stream)))
@@ -273,7 +277,7 @@ def efq_attn_fwd_expq(q, k, v, scale=None, causal=False, out=None, stream=None):
     sh = shape_of(q, k)
     scale = q.shape[-1] ** -0.5 if scale is None else scale
     out = torch.empty(q.shape, dtype=torch.float32, device=q.device) if out is None else out
-    ws, ws_n = _workspace(q, sh, causal, PGEN_EXPQ, False, None, stream)
+    ws, ws_n = _workspace(sh, causal, PGEN_EXPQ, False, None, stream)
     _check(lib().efq_attn_fwd_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), PGEN_EXPQ,
                                  Params(*PARAMS_MEAN), _ptr(out), ctypes.byref(sh), _ptr(ws), ws_n,
                                  _stream(stream)))
@@ -324,7 +328,7 @@ def attn_fwd_qk8(qhat, khat, vhat, shape: Shape, scale: Optional[float] = None,
     if out is None:
         out = torch.empty((shape.batch, shape.seq_q, shape.heads_q, shape.head_dim),
                           dtype=torch.float32, device=qhat.device)
-    ws, ws_n = _split_scratch(shape, causal, kind, True, qhat.device, stream)
+    ws, ws_n = _split_scratch(shape, causal, kind, True, stream)
     _check(lib().efq_attn_fwd_qk8_ws(_ptr(qhat), qhat.numel(), _ptr(khat), khat.numel(), _ptr(vhat),
                                      vhat.numel(), float(scale), int(causal), kind,
                                      _params(kind, params), _ptr(out), ctypes.byref(shape), _ptr(ws),
@@ -368,7 +372,7 @@ def attn_fwd_lowbit(q, k, v, scale: Optional[float] = None, causal: bool = False
         scale = q.shape[-1] ** -0.5
     if out is None:
         out = torch.empty(q.shape, dtype=torch.float32, device=q.device)
-    ws, ws_n = _workspace(q, sh, causal, kind, True, workspace, stream)
+    ws, ws_n = _workspace(sh, causal, kind, True, workspace, stream)
     _check(lib().efq_attn_fwd_lowbit_ex(_ptr(q), _ptr(k), _ptr(v), float(scale), int(causal), kind,
                                         _params(kind, params), _ptr(out), ctypes.byref(sh), _ptr(ws),
                                         ws_n, _stream(stream)))

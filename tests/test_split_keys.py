@@ -152,6 +152,28 @@ def test_entry_points_streams_and_capture(B):
 
 
 @pytest.mark.gpu
+def test_stream_given_as_a_bare_handle(B):
+    """An object with only a cuda_stream is taken as a stream: calls on it go
+    on without torch's memory, unsplit or with the library's own allocation."""
+    q, k, v = _inputs(2, 3, 4200, 8, 2, 128)
+    sh = B.shape_of(q, k)
+    vh = B.quant_v(v, seq_q=3, heads_q=8)
+    ref, low = B.attn_fwd_vhat(q, k, vh), B.attn_fwd_lowbit(q, k, v)
+    side = torch.cuda.Stream()
+
+    class Handle:
+        cuda_stream = side.cuda_stream
+
+    torch.cuda.synchronize()
+    out = B.attn_fwd_vhat(q, k, vh, stream=Handle())
+    whole = B.attn_fwd(q, k, v, stream=Handle())
+    lowbit = B.attn_fwd_lowbit(q, k, v, stream=Handle())
+    torch.cuda.synchronize()
+    assert float((out - ref).abs().max()) <= _bound(4200, v)
+    assert torch.equal(whole, ref) and torch.equal(lowbit, low)
+
+
+@pytest.mark.gpu
 def test_default_workspace(B):
     """Without a workspace the binding takes one from torch's allocator: calls
     in flight on two streams, and the size following the shape."""
