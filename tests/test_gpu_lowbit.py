@@ -242,8 +242,8 @@ def test_lowbit_all_rows(B, orc, wl):
 
 
 def test_lowbit_entry_points_agree(B):
-    """The one-call path (workspace or stream-ordered allocation) equals the
-    three quantisers followed by the MXFP8 attention."""
+    """The one-call path (the caller's workspace, or the binding's from torch's
+    allocator) equals the three quantisers followed by the MXFP8 attention."""
     w = inputs.Workload("c", 2, 4, 2, 300, 64, True, "qwen", 3)
     q, k, v = (t.cuda() for t in inputs.make_qkv(w))
     qh, kh = B.quant_qk(q, k)
