@@ -1507,11 +1507,11 @@ __device__ __forceinline__ void pp_schedule(PPWave<D, KIND, DUMP, Q8, true>& w, 
 // chain (M then V, ~2100 cycles for a wave alone on its SIMD, ~2450 for two)
 // and, with few keys, by the loads and stores around it, which the other
 // workgroup's tiles cover.  Against the eight-wave kernel the K and V~ tiles
-// are read twice as often and a tile costs 5-10 % more in the steady state;
+// are read twice as often and a tile costs 3-6 % more in the steady state;
 // it wins where that kernel leaves CUs idle or its workgroups are short
 // (use_half).  Kernel time, EFQ, 32/8 heads, D 128 causal, eight waves ->
-// this: 512 tokens 18.8 -> 13.5 us, 2048 tokens 46.3 -> 41.0 us, 16 prompts
-// of 333 tokens 55.6 -> 41.0 us; 8192 tokens 352 -> 372 us.
+// this: 512 tokens 17.9 -> 12.7 us, 2048 tokens 44.3 -> 38.2 us, 16 prompts
+// of 333 tokens 59.0 -> 44.6 us; 8192 tokens 354 -> 366 us.
 constexpr int kHWaves = 4;
 constexpr int kHP = 2;                     // tiles streamed ahead
 constexpr int kHK = kHP + 1;               // K ring depth
@@ -2771,33 +2771,43 @@ int launch_q8(const void* x, int B, int S, int H, int D, void* y, hipStream_t st
   return EFQ_OK;
 }
 
-// Whether the half-workgroup kernel takes a shape.  Timed side by side
-// (eight waves / half, us, EFQ unless noted):
-//  - no more eight-wave workgroups than CUs: the half workgroups spread over
-//    idle CUs or finish early ones (one prompt of 1500 / 2048 tokens, 32 heads
-//    32.8 / 28.8 and 43.8 / 38.4; 64 sequences' single queries against 4096 keys
-//    602 / 375, where seven of the eight waves have no query);
+// Whether the half-workgroup kernel takes a shape.  Timed side by side on one
+// card (eight waves / half, us; EFQ, bf16 Q K^T, D 128 and 32/8 heads unless
+// noted).  The lines were drawn before Q and O passed through LDS; where they
+// now leave a gain on their far side, that is said.
+//  - up to 128 queries: at least half of the eight waves have no query (64
+//    sequences' single queries against 4096 keys 575 / 371; 64 x 128 652 / 413).
 //    Not so the cheapest stage (EFQ) on bf16 keys that no other head shares,
 //    from HBM, where a CU has no second workgroup: the two tiles this kernel has
-//    in flight hide less of the latency than the other's four (24 heads, D 128,
-//    up to 112 workgroups: 4 x 16 queries, 30000 keys 388 / 421, 10000 keys 137 /
-//    144, but 8 x 16 queries, 6678 keys 119 / 108; 12 key/value heads 389 / 398).
-//  - few keys: loads and stores around the tiles weigh most (32760 x 128 / 512 /
-//    1024 keys, 24 heads: 196 / 166, 276 / 263, 396 / 406; 8 prompts of 1024
-//    tokens 90.8 / 84.0, of 2048 277 / 288);
-//  - MXFP8 Q K^T and causal: a tile reads half the K bytes, so the doubled
-//    reads cost little and the even spread of the causal lengths wins (4096
-//    83.9 / 80.1, 6000 168.9 / 163.9, but 16384 1021 / 1060).
-//  - non-causal, up to 1536 keys, and a grid of one to two rounds of the
-//    eight-wave kernel, whose second round is part empty (4 x 1500, 12 heads,
-//    D 64: 49.6 / 45.5; 8000 x 1024, 24 heads, in between: 96.2 / 94.7).
-//    With 129 to 255 eight-wave workgroups, one round, some CUs get two half
-//    workgroups and take as long as the eight waves do: what is left is the
-//    stage itself, and with more than 1024 keys EFQ is 1-4 % faster there, the
-//    LUT and, at D = 128, exp-then-quantize 1-4 % slower (1500 x 1500, 24 heads,
-//    D 128: EFQ 34.5 / 34.0, LUT 37.7 / 38.6, exp 40.9 / 42.2).
-// Elsewhere the eight-wave kernel is as fast or faster (4096 tokens causal
-// 107.5 / 111.3, 7000 x 7000 24 heads 415 / 449).
+//    in flight hide less of the latency than the other's four (24 heads, up to
+//    112 workgroups: 4 x 16 queries, 30000 keys 388 / 421, 10000 keys 137 / 144,
+//    but 8 x 16 queries, 6678 keys 119 / 108; 12 key/value heads 389 / 398).
+//  - few keys: the loads and stores around the tiles weigh most.  Causal up to
+//    1024 (16 prompts of 333 tokens 59 / 45, 8 of 1024 98 / 89; beyond, 8 of 1100
+//    113 / 100, of 2048 260 / 267), else up to 768 (32760 queries, 24 heads, 128
+//    keys 198 / 143, 512 273 / 233, 768 325 / 295; beyond, 1024 375 / 357, 1536
+//    488 / 477, 2048 591 / 605).
+//  - MXFP8 Q K^T and causal, up to 6144 keys: a tile reads half the K bytes, so
+//    the doubled reads cost little and the even spread of the causal lengths
+//    wins (4096 78.5 / 75.7, 6000 166 / 157; beyond, 8192 275 / 269, 12288 575 /
+//    574, 16384 986 / 990).
+//  - causal, no more eight-wave workgroups than CUs: the half workgroups spread
+//    over idle CUs, or long and short ones share one (1500 tokens 33.6 / 28.3,
+//    2048 43.7 / 37.7; beyond, 2300 49.2 / 45.0, 3000 63.7 / 63.0, 4096 101.0 /
+//    101.5, 8192 354 / 366).
+//  - non-causal, up to 1536 keys and two rounds of eight-wave workgroups, the
+//    second part empty (4 x 1500, 12 heads, D 64 47.9 / 42.7, 4000 x 1500, 24
+//    heads 72.4 / 65.7; beyond, 4000 x 2048 89.5 / 87.7, 8000 x 1024, three
+//    rounds, 93.3 / 89.2).  With 129 to 255 eight-wave workgroups, one round,
+//    some CUs get two half workgroups and take as long as the eight waves do:
+//    what is left is the stage itself, and with more than 1024 keys EFQ is 1-4 %
+//    faster there, the LUT and, at D = 128, exp-then-quantize 1-4 % slower (1500
+//    x 1500, 24 heads: EFQ 34.5 / 34.0, LUT 37.7 / 38.6, exp 40.9 / 42.2).
+// Elsewhere the eight-wave kernel is as fast or faster (7000 x 7000, 24 heads
+// 398 / 421).  The LUT stage at D = 128 holds 256 registers and keeps two to
+// four more in scratch from before the tile loop to after it; at the lines above
+// it gains what EFQ does (2048 tokens 47.0 / 40.2, 8 x 1024 101 / 92, 32760 x 512
+// 281 / 240).
 bool use_half(const efq_shape* s, int causal, int kind, bool q8) {
 #if EFQ_PHASE_STAMPS
   return false;   // the stamped build records the eight-wave kernel
@@ -2854,12 +2864,12 @@ AttnArgs attn_args(const efq_shape* s, float scale, int causal, efq_params p, bo
   a.spread = half && causal ? work_order(total, (long)a.B * a.Hq) : 0;
   a.sq_pad = (int)pad64(s->seq_q);
   a.sk_pad = (int)pad64(s->seq_k);
-  // A grid with more half workgroups than the CUs hold is bound by how fast
-  // they follow one another; a smaller one by one workgroup's own latency,
-  // which the pass through LDS and its barrier lengthen (512 tokens, 32 heads:
-  // 12.7 us without, 13.1 with; 32760 x 512, 24 heads: 244.5 / 232.6).
-  // With many keys the store is a small part, and direct is as fast (4096
-  // tokens, MXFP8, LUT: 83.4 / 84.5).
+  // The pass through LDS pays where the stores are a large part and many
+  // workgroups follow one another (direct / rows, us): 8 prompts of 512 tokens,
+  // 32 heads 38.0 / 35.7, 32760 x 512, 24 heads 254 / 233, 4000 x 1500 68.9 / 66.1.
+  // Beyond the line there is little to gain: a grid that is resident at once 18.3
+  // / 17.6 (4 x 512), 28.4 / 28.2 (1500), 12.7 / 12.7 (512), more keys 47.8 / 47.1
+  // (3000, MXFP8), 76.0 / 75.7 (4096; LUT 81.5 / 81.8).
   a.o_rows = total > 2 * kCUs && s->seq_k <= 1536;
   a.q8_soff = q8_scale_offset(qhat_rows(s), s->head_dim);
   a.k8_soff = q8_scale_offset(khat_rows(s), s->head_dim);
