@@ -527,16 +527,16 @@ struct Q8Args {
   size_t soff;
 };
 
-// Byte offsets in Q^ (K^) of the codes of part `part` (8 elements) of a row,
-// and of its block's scale from the scales' start: 64-bit whatever the type of
-// the row index, since the codes pass 4 GiB long before the thread index does.
-template <typename IDX>
-__host__ __device__ __forceinline__ size_t q8_code_at(IDX row, int D, int part) {
-  return (size_t)row * D + part * 8;
+// Byte offsets in Q^ (K^) of the codes a thread writes, and, from the scales'
+// start, of its 32-element block's scale.  Threads follow one another through
+// the rows, 8 codes each, so thread n writes codes 8 n and scale n / 4; 64-bit
+// (the codes pass 4 GiB long before the thread index does), with the
+// workgroup's part scalar.
+__host__ __device__ __forceinline__ size_t q8_code_at(unsigned block, unsigned thread) {
+  return (size_t)block * 2048 + thread * 8;
 }
-template <typename IDX>
-__host__ __device__ __forceinline__ size_t q8_scale_at(IDX row, int D, int part) {
-  return (size_t)row * (D / 32) + (part >> 2);
+__host__ __device__ __forceinline__ size_t q8_scale_at(unsigned block, unsigned thread) {
+  return (size_t)block * 64 + (thread >> 2);
 }
 
 // One thread per 8 elements (4 threads per 32-element block, lanes 4i..4i+3);
@@ -579,8 +579,8 @@ __device__ __forceinline__ void mxfp8_block(const unsigned short* __restrict__ x
   w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, y2(2, 0), y2(2, 1), 1.0f, false);
   w1 = __builtin_amdgcn_cvt_scalef32_pk_fp8_f32(w1, y2(3, 0), y2(3, 1), 1.0f, true);
   const unsigned w[2] = {__builtin_bit_cast(unsigned, w0), __builtin_bit_cast(unsigned, w1)};
-  *(uint2*)(y + q8_code_at(row, a.D, part)) = make_uint2(w[0], w[1]);
-  if ((part & 3) == 0) y[a.soff + q8_scale_at(row, a.D, part)] = (uint8_t)(k + 127);
+  *(uint2*)(y + q8_code_at(block, threadIdx.x)) = make_uint2(w[0], w[1]);
+  if ((part & 3) == 0) y[a.soff + q8_scale_at(block, threadIdx.x)] = (uint8_t)(k + 127);
 }
 
 template <typename IDX>

@@ -20,21 +20,24 @@ def _function(src, head):
 
 def test_offsets_and_launch_rule(tmp_path):
     src = open(SRC).read()
-    code = "template <typename IDX>\n" + _function(src, "__host__ __device__ __forceinline__ size_t q8_code_at(")
-    scale = "template <typename IDX>\n" + _function(src, "__host__ __device__ __forceinline__ size_t q8_scale_at(")
+    code = _function(src, "__host__ __device__ __forceinline__ size_t q8_code_at(")
+    scale = _function(src, "__host__ __device__ __forceinline__ size_t q8_scale_at(")
     fits = _function(src, "bool fits_launch(")
     # the kernel stores through the helpers, the merged launch asks the rule
-    assert "y + q8_code_at(row, a.D, part)" in src and "y[a.soff + q8_scale_at(row, a.D, part)]" in src
+    assert "y + q8_code_at(block, threadIdx.x)" in src and "y[a.soff + q8_scale_at(block, threadIdx.x)]" in src
     assert "!fits_launch(nv + nq + nk)" in src
     prog = tmp_path / "q8.cpp"
-    prog.write_text("#include <cstddef>\n#include <initializer_list>\n#define __host__\n#define __device__\n#define __forceinline__ inline\n"
+    prog.write_text("#include <cstddef>\n#include <initializer_list>\n"
+                    "#define __host__\n#define __device__\n#define __forceinline__ inline\n"
                     + code + scale + fits + """
 int main() {
-  for (int D : {64, 128})
-    for (unsigned row : {0u, 1u, 0x01ffffffu, 0x02000000u, 0x03ffffffu, 0x04000001u, 0x0fffffffu})
-      for (int part = 0; part < D / 8; ++part) {
-        if (q8_code_at(row, D, part) != (unsigned long long)row * D + 8ull * part) return 1;
-        if (q8_scale_at(row, D, part) != (unsigned long long)row * (D / 32) + part / 4) return 2;
+  typedef unsigned long long u64;
+  for (int D : {64, 128})   // thread n holds part n % (D / 8) of row n / (D / 8)
+    for (unsigned block : {0u, 1u, 0x000fffffu, 0x001fffffu, 0x00200000u, 0x00200001u, 0x00fffffeu, 0x01ffffffu})
+      for (unsigned t = 0; t < 256; ++t) {
+        const u64 n = (u64)block * 256 + t, row = n / (D / 8), part = n % (D / 8);
+        if (q8_code_at(block, t) != row * D + 8 * part) return 1;
+        if (q8_scale_at(block, t) != row * (D / 32) + part / 4) return 2;
       }
   for (long n : {1L, 16384L, (1L << 24) - 1, 1L << 24, 1L << 25, 0x7fffffffL})
     if (fits_launch(n) != (n * 256 < (1L << 32))) return 3;
