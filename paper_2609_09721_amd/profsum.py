@@ -17,6 +17,16 @@ stats TRACE_DIR OUT_FILE WORKLOAD COMMAND...
     configuration (efq_avg_us) with the kernel-source hash, which bench.py
     reports beside its own HIP-event average.
 
+case-run NAME
+    Five passes of one workload of perf/cases.py, for a trace or a counter pass.
+
+cases OUT_FILE NAME... -- DIR
+    Per kernel of those workloads, from DIR/<name>/{t,a,f,w}: a kernel trace and
+    the counter passes named in the file: median time, matrix-core busy and
+    VALU-active cycles, LDS bank conflicts, bytes read and written (FETCH_SIZE and
+    WRITE_SIZE in units of 2048 and 1024 bytes, what a device copy of known size
+    reads here) and their rate.
+
 sweep JSONL OUT_FILE COMMAND...
     Table of a `bench.py --sweep` run (one JSON line per sequence length).
 
@@ -214,7 +224,83 @@ def counters(dirs, out: str, workload: str, command: str):
     print(open(out).read())
 
 
+OWN = ("attn_pp_kernel", "split_", "vquant_kernel", "mxfp8_kernel", "lowbit_quant_kernel", "rho_final_kernel")
+PASSES = {"t": "--kernel-trace --stats", "f": "--pmc FETCH_SIZE", "w": "--pmc WRITE_SIZE",
+          "a": "--pmc SQ_VALU_MFMA_BUSY_CYCLES SQ_ACTIVE_INST_VALU SQ_INSTS_LDS SQ_LDS_BANK_CONFLICT SQ_WAVES GRBM_GUI_ACTIVE"}
+RUNS = 5
+
+
+def case_run(name: str):
+    import torch
+    from perf import cases
+    case = next(c for c in cases.listed() if c["name"] == name)
+    state = cases.prepare(case, 1)
+    torch.cuda.synchronize()
+    for _ in range(RUNS):
+        cases.run(state)
+    torch.cuda.synchronize()
+
+
+def _own(name: str):
+    n = name.replace("(anonymous namespace)::", "").replace("void ", "").split("(")[0]
+    return n if n.startswith(OWN) else None
+
+
+def case_rows(d: str):
+    """{kernel: {"us": [..], counter: [..]}} of one workload's passes."""
+    rows = {}
+    for f in glob.glob(os.path.join(d, "t", "**", "*kernel_trace.csv"), recursive=True):
+        for r in sorted(csv.DictReader(open(f)), key=lambda r: int(r["Dispatch_Id"])):
+            if _own(r["Kernel_Name"]):
+                us = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3
+                rows.setdefault(_own(r["Kernel_Name"]), {}).setdefault("us", []).append(us)
+    for p in "afw":
+        for c in (PASSES[p].split()[1:]):
+            for name, val in per_dispatch(os.path.join(d, p), c):
+                if _own(name):
+                    rows.setdefault(_own(name), {}).setdefault(c, []).append(val)
+    return rows
+
+
+def cases_summary(out: str, names, d: str):
+    import bench
+    with open(out, "w") as fh:
+        fh.write("# kernels of workloads of perf/cases.py, bf16 unless named otherwise there\n")
+        fh.write("# commands (from the repository root, TMPDIR=/tmp), for every workload and pass:\n")
+        for p, opts in PASSES.items():
+            fh.write(f"#   rocprofv3 {opts} -d <DIR>/<name>/{p} -o p --output-format csv -- "
+                     "python3 -m paper_2609_09721_amd.profsum case-run <name>\n")
+        fh.write("#   python3 -m paper_2609_09721_amd.profsum cases <OUT> <names> -- <DIR>\n")
+        fh.write("# attn_pp_kernel template: <head_dim, pgen kind, causal, dump, MXFP8 Q K^T, waves per workgroup, "
+                 "calibration sums>\n")
+        fh.write("# medians; MFMA busy and VALU active per SIMD cycle of the kernel; conflicts: LDS bank-conflict "
+                 "cycles per LDS instruction\n")
+        fh.write("# workload | kernel | launches a pass | us | MFMA busy | VALU active | waves | conflicts | "
+                 "MB read | MB written | TB/s\n")
+        for name in names:
+            for k, r in case_rows(os.path.join(d, name)).items():
+                if len(r["us"]) < RUNS:      # what prepare() launched
+                    continue
+                m = lambda c: sorted(r[c])[len(r[c]) // 2] if r.get(c) else float("nan")
+                cyc = m("GRBM_GUI_ACTIVE") / 8
+                rd, wr = m("FETCH_SIZE") * 2048 / 1e6, m("WRITE_SIZE") * 1024 / 1e6
+                fh.write(f"{name} | {k} | {len(r['us']) // RUNS} | {m('us'):.1f} | "
+                         f"{m('SQ_VALU_MFMA_BUSY_CYCLES') / 1024 / cyc:.3f} | "
+                         f"{4 * m('SQ_ACTIVE_INST_VALU') / 1024 / cyc:.3f} | {m('SQ_WAVES'):.0f} | "
+                         f"{m('SQ_LDS_BANK_CONFLICT') / max(m('SQ_INSTS_LDS'), 1):.3f} | {rd:.1f} | {wr:.1f} | "
+                         f"{(rd + wr) / m('us'):.2f}\n")
+        fh.write(f"kernel_hash = {bench.kernel_hash()}\n")
+    print(open(out).read())
+
+
 def main():
+    if sys.argv[1] == "case-run":
+        case_run(sys.argv[2])
+        return
+    if sys.argv[1] == "cases":
+        cut = sys.argv.index("--")
+        cases_summary(sys.argv[2], sys.argv[3:cut], sys.argv[cut + 1])
+        return
     if sys.argv[1] == "counters":
         rest = sys.argv[4:]
         cut = rest.index("--")
